@@ -4,14 +4,11 @@ One step = pss_forward + pss_backward_update (forward gather/pool, backward
 deposit, optimizer step) over one batch of synthetic bags, rotating 4
 pre-generated index batches and gradient batches resident in HBM.  The
 forward is called with PSS_PREPARE_BACKWARD, as a training step can: on the
-headline workload its streamed kernel writes the first stage of the
-backward's grouping (keys, rows, digit counts) while it reads the batch's
-index and offset entries, and the backward finishes the grouping (379.7
-against 391.3 us per step without the flag, on one box).  --no-prepare: the
-backward groups the batch itself.  --prepare: each step starts with
-pss_prepare_backward instead, the whole grouping on a library stream beside
-the forward kernel (slower there: it shares the memory system with a
-forward that writes at the streamed rate).
+headline workload the first stage of the backward's grouping then runs just
+ahead of the forward kernel, which finds the batch's index and offset
+entries in the caches.  --no-prepare: the backward groups the batch itself.
+--prepare: each step starts with pss_prepare_backward instead, the whole
+grouping on a library stream beside the forward kernel.
 
 Default workload: criteo-tb-shaped one-hot batch (26 tables with log-uniform
 cardinalities in [3, 4e7], Zipf(1.1) indices, batch 65536, d = 128, Z = 32,
@@ -22,7 +19,8 @@ Prints one JSON line on stdout; diagnostics go to stderr.
                  index) row: d gathered, pooled, d deposited)
   roofline       the dominant kernel's floor bytes per launch over its
                  average duration (HIP events on the launch stream, around the
-                 pss_forward call, which enqueues that one kernel there) vs the
+                 pss_forward call: that kernel, and the grouping's first stage
+                 when the forward prepares the backward) vs the
                  peak of the memory level that bounds it; step_* fields give
                  the same for the whole step.  Floor bytes per level: HBM
                  carries the index/offset/row streams and the dense optimizer
@@ -401,14 +399,14 @@ def main():
     timed = {lv: v for lv, v in levels.items() if v["t_star_us"] is not None}
     step_bound = max(timed, key=lambda lv: timed[lv]["t_star_us"])
     t_star = timed[step_bound]["t_star_us"] * 1e-6
-    # Kernels timed live: pss_forward launches exactly one kernel (events
-    # around the call time it); the library has the reduce-and-deposit
+    # Kernels timed live: events around the pss_forward call time its kernel
+    # (with the first stage of the backward's grouping when it is prepared
+    # there: the figure is then that much too long); the library has the reduce-and-deposit
     # kernel's dispatch record events at its start and end on request.  Each kernel's bound is the level
     # whose floor time is largest for its own bytes; the roofline object
     # describes the longer of the two (the dominant kernel), and both are
     # listed under "kernels".  Kernel names are those the committed counters
-    # recorded (pss_forward launches the streamed or the tiled kernel, by the
-    # batch's shape).
+    # recorded.
     fwd_lv = max(timed, key=lambda lv: timed[lv]["forward_bytes"] / peaks_gbs[lv][0])
     pmc = forward_counters(wl.name)
     kernels = {"forward": {

@@ -70,12 +70,11 @@
  *     invalid with ATOMIC or SPARSE (PSS_ERR_UNSUPPORTED).
  *   PSS_PREPARE_BACKWARD  read by pss_forward only (the other calls ignore
  *     it; pss_prepare_backward does the same work as a call of its own): the
- *     forward also groups the batch's lookups by token for the backward.  A
- *     forward that runs its streamed kernel (one item per bag, d in {64,
- *     128, 256}, Z % 4 == 0, the shared array within 32 MiB) writes the
- *     grouping's first stage (every lookup's key and pooled row, and the
- *     first radix pass's digit counts) from that kernel, on `stream`, while
- *     it reads the batch's index and offset entries; the backward finishes
+ *     forward also groups the batch's lookups by token for the backward.  For
+ *     a batch with as many items as bags the grouping's first stage (every
+ *     lookup's key and pooled row, and the first radix pass's digit counts)
+ *     runs on `stream` ahead of the forward kernel, which then finds the
+ *     batch's index and offset entries in the caches; the backward finishes
  *     the grouping on its stream.  Other forwards group the batch on a
  *     library-owned stream that runs beside the forward kernel.  The next
  *     pss_backward_update on the same stream uses that grouping when its

@@ -256,11 +256,11 @@ class CallScratch {
 // grouping waits for `start`, recorded after every earlier call on the
 // caller's stream (including the backward that read the buffer).
 //
-// A forward that runs the streamed kernel writes the grouping's first stage
-// (keygen) itself instead (`fused`): it reads the batch's index and offset
-// entries anyway.  Everything then happens on the caller's stream (no side
-// stream, no events), and the backward finishes the grouping (the radix
-// pass) before its reduction.
+// For a batch with as many items as bags the call runs the grouping's first
+// stage (keygen) on the caller's stream ahead of the forward kernel instead
+// (`fused`).  Everything then happens on that stream (no side stream, no
+// events), and the backward finishes the grouping (the radix pass) before
+// its reduction.
 struct Prepared {
   std::mutex mu;
   hipStream_t side = nullptr;
@@ -269,7 +269,7 @@ struct Prepared {
   void* buf = nullptr;
   size_t bytes = 0;
   bool valid = false;  // a grouping waits for its backward
-  bool fused = false;  // valid: its keygen stage was written by the forward kernel
+  bool fused = false;  // valid: its keygen stage was run by the forward call
   const void* indices = nullptr;
   const void* offsets = nullptr;
   KParams made{};
@@ -352,8 +352,8 @@ int prepare_backward(const KParams& p, const void* indices, const void* offsets,
   return PSS_OK;
 }
 
-// Sets up the slot for a grouping whose keygen stage the streamed forward
-// kernel writes on the caller's stream (the buffer is allocated, and an
+// Sets up the slot for a grouping whose keygen stage the forward call
+// runs on the caller's stream (the buffer is allocated, and an
 // unused earlier grouping dropped, in stream order); *kg gets the stage's
 // layout in the slot's buffer.  The slot becomes valid only through
 // mark_fused, once the forward kernel has been enqueued.
@@ -403,7 +403,7 @@ void mark_fused(Prepared* pr) {
 
 // The grouped pairs of a prepared grouping, on `stream`: wait for the
 // library stream's grouping, or finish the one whose keygen stage the
-// forward wrote.
+// forward call ran.
 hipError_t prepared_pairs(Prepared* prep, const KParams& p, hipStream_t stream,
                           pss::GroupedPairs* pairs) {
   if (prep->fused) return pss::finish_group_sorted(p, prep->buf, true, stream, pairs);
@@ -539,7 +539,7 @@ hipError_t enqueue_backward(const BackwardPlan& plan, void* shared, float* state
     hipError_t e = hipSuccess;
     if (prep != nullptr) {
       // the grouping made ahead (on the library stream, or begun by the
-      // forward kernel)
+      // forward call)
       e = prepared_pairs(prep, p, stream, &pairs);
     } else {
       e = pss::launch_group_sorted(p, indices, offsets, group_ws, stream, &pairs);
@@ -565,7 +565,7 @@ hipError_t enqueue_backward(const BackwardPlan& plan, void* shared, float* state
   if (!plan.fused) e = pss::launch_zero(dst, M, stream);
   if (e == hipSuccess && prep != nullptr) {
     // the grouping made ahead (on the library stream, or begun by the
-    // forward kernel)
+    // forward call)
     pss::GroupedPairs pairs;
     e = prepared_pairs(prep, p, stream, &pairs);
     if (e == hipSuccess) e = pss::launch_reduce_sorted(dst, scale, p, pairs, grad_out, stream);
@@ -654,9 +654,9 @@ int pss_forward(const void* shared, int64_t M, int32_t Z, int32_t d,
   Prepared* fused = nullptr;
   if ((hash_params->flags & PSS_PREPARE_BACKWARD) && p.N > 0 && groups_by_token(M, p, hash_params) &&
       !capturing(stream)) {
-    // the streamed kernel writes the grouping's keygen stage itself; other
-    // forwards leave the grouping to the library stream
-    if (pss::forward_streams(p, bf16)) {
+    // as many items as bags: the first stage runs ahead of the forward
+    // kernel, on `stream`; other batches are grouped on the library stream
+    if (pss::keygen_counts(p)) {
       if (prepare_fused(p, indices, offsets, stream, &kg, &fused) != PSS_OK) {
         (void)hipGetLastError();
         fused = nullptr;
@@ -665,8 +665,10 @@ int pss_forward(const void* shared, int64_t M, int32_t Z, int32_t d,
       (void)hipGetLastError();
     }
   }
-  const hipError_t e = pss::launch_forward(shared, bf16, p, indices, offsets, out, stream,
-                                           fused != nullptr ? &kg : nullptr);
+  hipError_t e = hipSuccess;
+  if (fused != nullptr) e = pss::launch_keygen_counts(p, indices, offsets, kg, stream);
+  if (e == hipSuccess)
+    e = pss::launch_forward(shared, bf16, p, indices, offsets, out, stream, fused != nullptr);
   if (e == hipSuccess && fused != nullptr) mark_fused(fused);
   return hip_status(e);
 }

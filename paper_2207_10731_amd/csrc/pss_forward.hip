@@ -1,39 +1,44 @@
 // Forward of the PSS layer: hash -> chunk gather -> sum-pool (paper Sec. 2.4
 // forward(i) = (S e_i)^T M with the ROBE-Z mapping of Sec. 2.5).
 //
-// Two kernels.  Batches of one item per bag with d in {64, 128, 256},
-// Z % 4 == 0 and an array within the aggregate L2 take the streamed forward
-// (end of this file), which writes the output in row order.  Every other
-// batch takes the tiled kernel: one wavefront per tile of 64 bags of one
-// table.  Hashing: with C = d/Z <= 16 chunks, each lane evaluates the C chunk
-// bases of one item of the current 64-item block into a wave-private LDS
-// table and the gathers read their base from it (one modular reduction per
-// chunk instead of one per dim); with more chunks each lane hashes its own
-// dims (item part on the scalar unit).  U items are gathered before any is
-// consumed so that U * EPL loads per lane are in flight.  Pooling runs in registers in
-// item order; a finished bag's row is written with non-temporal stores (the
-// 4 bytes/dim output stream must not evict the shared array from L2/MALL).
-// On gfx9 stores and loads share one wait counter, so the kernel issues all
-// U gathers of a batch before any store of that batch: a store is never
-// followed by a wait for a load issued after it.
+// Three kernels, all bound by the memory system (rows written, chunks
+// gathered):
+//   rows   one item per bag (as many items as bags): a wavefront takes a run
+//          of consecutive bags of a table, a lane group holds one row;
+//   bags   any other batch: a lane group pools one bag;
+//   tiled  one item per bag, at least 2^20 bags and an array beyond the
+//          aggregate L2: a wavefront takes 64 bags, sorts their tokens and
+//          gathers each distinct one once.
+// Rows are written with non-temporal stores: the output stream must not
+// evict the shared array from the L2s and the memory-side cache (plain
+// stores: 254 against 173 us on 26 x 65536 rows of 512 bytes).
 //
 // Options: SIGN (template) multiplies each chunk by its sign factor and skips
 // chunks of factor 0; mean pooling divides a finished row by the bag's item
 // count; rows may be stored as bfloat16 (round to nearest even); indices and
 // offsets may be int32.
-#include <atomic>
-
-#include "pss_keygen.hpp"
 #include "pss_launch.hpp"
 
 namespace pss {
 
-// Shared arrays larger than the chip's aggregate L2 (8 x 4 MiB) get their
-// tiles partitioned over the XCDs (see forward_kernel).  Measured: the
-// multi-hot forward on a 64 MB array 1053 -> 867 us, the row-hash forward
-// on a 128 MB array 852 -> 832 us; on a 10 MB array the split is neutral
-// alone and slower beside a concurrent backward grouping.
-constexpr uint64_t kXcdSplitBytes = 32ull << 20;
+// The row kernels give each XCD a contiguous share of the batch (see
+// xcd_block) whatever the array's size: its L2 then holds the hot tokens of
+// about 1/kXcds of the tables (26 x 65536 one-hot rows, 10 MB array: 173 ->
+// 169 us, 26 x 16384: 48.9 -> 45.4 us).
+//
+// Workgroups are dispatched round-robin over the chip's XCDs (workgroup b on
+// XCD b mod kXcds), each with an L2 of its own.  grid.x is a multiple of
+// kXcds; any other dispatch order only changes which L2 sees which part.
+__device__ __forceinline__ uint64_t xcd_block() {
+  return (blockIdx.x % kXcds) * static_cast<uint64_t>(gridDim.x / kXcds) + blockIdx.x / kXcds;
+}
+
+// Arrays beyond the chip's aggregate L2 (8 x 4 MiB): see tiled_applies.
+constexpr uint64_t kL2Bytes = 32ull << 20;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));        // 4-byte aligned
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));     // 2-byte aligned
 
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
   const uint32_t lo = readlane_u32(static_cast<uint32_t>(v), lane);
@@ -41,13 +46,386 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Pooled value k of the output: float32, or bfloat16 rounded to nearest even.
-__device__ __forceinline__ void store_out(void* out, uint64_t k, float v, uint32_t bf16) {
-  if (bf16)
-    __builtin_nontemporal_store(f32_to_bf16_rne(v), static_cast<uint16_t*>(out) + k);
-  else
-    __builtin_nontemporal_store(v, static_cast<float*>(out) + k);
+// Cached loads of indices[e] / offsets[g] (wave-uniform choice of width): a
+// line of indices serves several lane groups.
+__device__ __forceinline__ uint32_t index_at(const void* idx, uint64_t e, uint32_t i32) {
+  return i32 ? static_cast<uint32_t>(static_cast<const int32_t*>(idx)[e])
+             : static_cast<uint32_t>(static_cast<const int64_t*>(idx)[e]);
 }
+__device__ __forceinline__ int64_t offset_at(const void* off, uint64_t g, uint32_t i32) {
+  return i32 ? static_cast<int64_t>(static_cast<const int32_t*>(off)[g])
+             : static_cast<const int64_t*>(off)[g];
+}
+
+// The first `touch_blocks` workgroups read the batch's index and offset
+// arrays once, in whole 16-byte pieces lying inside them, before their own
+// work.  After a backward the arrays lie in HBM, where the index loads of
+// the later wavefronts would queue behind the write stream; read up front at
+// the streaming rate they are found in the memory-side cache (26 x 65536
+// rows in a training step: 252 -> 176 us; 26 x 16384: 58.8 -> 46.6 us).
+constexpr uint32_t kTouchBlocks = 256;      // one workgroup per compute unit
+constexpr uint64_t kTouchBags = 1ull << 18;  // smaller batches run in one generation of workgroups
+__device__ __forceinline__ void touch_batch(const KParams& p, const void* __restrict__ indices,
+                                            const void* __restrict__ offsets,
+                                            void* __restrict__ out, const uint32_t touch_blocks) {
+  if (blockIdx.x >= touch_blocks || blockIdx.y != 0) return;
+  const uint64_t es = p.idx32 ? 4 : 8;
+  uint32_t seen = 0;
+  auto touch = [&](const void* base, uint64_t n_entries) {
+    const uint64_t a0 = reinterpret_cast<uint64_t>(base);
+    const uint64_t c_lo = (a0 + 15) / 16, c_end = (a0 + n_entries * es) / 16;
+    constexpr int kPieces = 16;  // requested before any is used
+    const uint64_t stride = static_cast<uint64_t>(touch_blocks) * kBlockThreads;
+    for (uint64_t c0 = c_lo + static_cast<uint64_t>(blockIdx.x) * kBlockThreads + threadIdx.x;
+         c0 < c_end; c0 += kPieces * stride) {
+      uint4 v4[kPieces];
+#pragma unroll
+      for (int k = 0; k < kPieces; ++k) {
+        const uint64_t c = c0 + k * stride;
+        v4[k] = c < c_end ? *reinterpret_cast<const uint4*>(c * 16) : uint4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int k = 0; k < kPieces; ++k) seen ^= v4[k].x ^ v4[k].y ^ v4[k].z ^ v4[k].w;
+    }
+  };
+  touch(indices, static_cast<uint64_t>(p.N));
+  touch(offsets, p.num_bags + 1);
+  // never true (N >= 0): keeps the loads
+  if (seen == 0x9e3779b9u && p.N < 0) static_cast<uint32_t*>(out)[threadIdx.x] = seen;
+}
+
+// ---------------------------------------------------------------------------
+// Rows and bags.  LPB lanes (a power of two) hold one pooled row, V
+// consecutive elements per lane, so that a wavefront works on GP = 64 / LPB
+// rows at once and one load per lane gathers a whole item.  V = 4 (one
+// 16-byte load; 8 bytes of bfloat16) when the chunk size is a multiple of 4: a
+// chunk then never splits a lane's elements.  V = 1 otherwise.  Wider rows
+// are cut into slabs of LPB * V elements (blockIdx.y).
+//
+// The chunk entries (hashed base and sign) of the items in hand are
+// evaluated once each, spread over the lanes, into a wave-private LDS table:
+// the lanes that share a chunk would otherwise all repeat its modular
+// reductions.
+// ---------------------------------------------------------------------------
+
+// Items a lane group has in flight: 8 pieces of 16 bytes per lane keep the
+// kernels within 64 VGPRs, 8 wavefronts per SIMD.  16 in flight (half the
+// wavefronts) gained 2% on long bags and lost 15% on short ones; 4 lost 1%
+// on 26 x 65536 rows.
+template <int V, int LPB> constexpr int row_batch() { return LPB >= 8 ? 8 : 4; }
+
+template <int V> struct Piece;
+template <> struct Piece<4> { typedef f32x4 type; };
+template <> struct Piece<1> { typedef float type; };
+
+template <bool SIGN>
+__device__ __forceinline__ uint32_t entry_base(uint32_t ent) {
+  return SIGN ? (ent != kSkip ? ent & 0x7fffffffu : 0u) : ent;
+}
+
+// Whether elements kk .. kk + V - 1 of the chunk of `ent` run past the end
+// of the array in the middle of a lane's piece (a single element wraps as a
+// whole).
+template <int V, bool SIGN>
+__device__ __forceinline__ bool splits(uint32_t ent, uint32_t kk, uint32_t M) {
+  return V > 1 && entry_base<SIGN>(ent) + kk + (V - 1) >= M;  // < 2M <= 2^32
+}
+
+// Elements kk .. kk + V - 1 of the chunk of `ent`, widened, unsigned; the
+// piece must not be split by the end of the array.
+template <typename WT, int V, bool SIGN>
+__device__ __forceinline__ typename Piece<V>::type gather(const WT* __restrict__ w, uint32_t ent,
+                                                          uint32_t kk, uint32_t M) {
+  const uint32_t base = entry_base<SIGN>(ent);
+  if constexpr (V == 1) {
+    return load_weight(w, wrap_add(base, kk, M));
+  } else {
+    const uint32_t m = SIGN && ent == kSkip ? 0u : base + kk;
+    if constexpr (sizeof(WT) == 4) {
+      return *reinterpret_cast<const f32x4u*>(reinterpret_cast<const float*>(w) + m);
+    } else {
+      const u32x2u b = *reinterpret_cast<const u32x2u*>(w + m);
+      return f32x4{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u),
+                   __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
+    }
+  }
+}
+
+// The same for any piece, element by element.
+template <typename WT, int V, bool SIGN>
+__device__ __forceinline__ typename Piece<V>::type gather_split(const WT* __restrict__ w,
+                                                                uint32_t ent, uint32_t kk,
+                                                                uint32_t M) {
+  const uint32_t base = entry_base<SIGN>(ent);
+  if constexpr (V == 1) {
+    return load_weight(w, wrap_add(base, kk, M));
+  } else {
+    return f32x4{load_weight(w, wrap_add(base, kk, M)), load_weight(w, wrap_add(base, kk + 1, M)),
+                 load_weight(w, wrap_add(base, kk + 2, M)), load_weight(w, wrap_add(base, kk + 3, M))};
+  }
+}
+
+__device__ __forceinline__ float flip(float x, uint32_t neg) {
+  return __uint_as_float(__float_as_uint(x) ^ neg);
+}
+template <bool SIGN>
+__device__ __forceinline__ float sign_piece(float x, uint32_t ent) {
+  if (!SIGN) return x;
+  return ent == kSkip ? 0.f : flip(x, ent & 0x80000000u);
+}
+template <bool SIGN>
+__device__ __forceinline__ f32x4 sign_piece(f32x4 x, uint32_t ent) {
+  if (!SIGN) return x;
+  if (ent == kSkip) return f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint32_t neg = ent & 0x80000000u;
+  return f32x4{flip(x.x, neg), flip(x.y, neg), flip(x.z, neg), flip(x.w, neg)};
+}
+
+// Elements e .. of the output: float32, or bfloat16 rounded to nearest even.
+__device__ __forceinline__ void store_piece(void* __restrict__ out, uint64_t e, float v,
+                                            uint32_t bf16) {
+  if (bf16)
+    __builtin_nontemporal_store(f32_to_bf16_rne(v), static_cast<uint16_t*>(out) + e);
+  else
+    __builtin_nontemporal_store(v, static_cast<float*>(out) + e);
+}
+__device__ __forceinline__ void store_piece(void* __restrict__ out, uint64_t e, f32x4 v,
+                                            uint32_t bf16) {
+  if (bf16) {
+    const u32x2u x = {static_cast<uint32_t>(f32_to_bf16_rne(v.x)) |
+                          (static_cast<uint32_t>(f32_to_bf16_rne(v.y)) << 16),
+                      static_cast<uint32_t>(f32_to_bf16_rne(v.z)) |
+                          (static_cast<uint32_t>(f32_to_bf16_rne(v.w)) << 16)};
+    __builtin_nontemporal_store(x, reinterpret_cast<u32x2u*>(static_cast<uint16_t*>(out) + e));
+  } else {
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4u*>(static_cast<float*>(out) + e));
+  }
+}
+
+// The lane's elements of a row: dims c .. c + V - 1 of slab blockIdx.y, in
+// chunk jc at offset kk; the slab meets the Cs chunks from j0 on (Cs <= LPB:
+// every chunk holds at least V dims of it).
+template <int V, int LPB>
+struct RowLane {
+  uint32_t c, kk, jc, j0, Cs;
+  bool act;
+  __device__ __forceinline__ RowLane(const KParams& p, int gl) {
+    const uint32_t c0 = blockIdx.y * (LPB * V);
+    c = c0 + static_cast<uint32_t>(gl) * V;
+    act = c < p.d;
+    j0 = c0 / p.Z;
+    const uint32_t dend = p.d < c0 + LPB * V ? p.d : c0 + LPB * V;
+    Cs = (dend - 1) / p.Z - j0 + 1;
+    const uint32_t cc = act ? c : c0;
+    jc = cc / p.Z;
+    kk = cc - jc * p.Z;
+  }
+};
+
+// Chunk entry of chunk j of the item with hash h.
+template <bool SIGN>
+__device__ __forceinline__ uint32_t item_entry(const KParams& p, uint32_t h, uint32_t j) {
+  const uint32_t base = fast_mod(add_mod_p(h, chunk_step(p.a, j)), p.fm_c, p.M);
+  if (!SIGN) return base;
+  return chunk_entry<SIGN>(
+      base, add_mod_p(sign_hash0(h, p.s_alpha, p.s_beta), chunk_step(p.a2, j)), p);
+}
+
+// The wavefront's LDS table has been written (or read): order it against
+// the next reads (or writes).
+__device__ __forceinline__ void table_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Any batch: one lane group per bag, items in order.  Lane i < U of the
+// group requests the index of item i of the next batch of U items while this
+// one is gathered.  Measured against the tiled kernel that pooled a tile of
+// 64 bags per wavefront before: 23101 bags of 9 items on average (d = 96, Z = 8,
+// bfloat16) 111 -> 24 us (that kernel filled 361 wavefronts), 852 K bags of 20
+// items (d = 64, Z = 16, 64 MB array) 889 -> 811 us: the rate of random
+// 64-byte requests beyond the L2s.
+template <typename WT, int V, int LPB, bool SIGN>
+__global__ __launch_bounds__(kBlockThreads) void forward_bags_kernel(
+    const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
+    const void* __restrict__ offsets, void* __restrict__ out) {
+  constexpr int U = row_batch<V, LPB>();
+  constexpr int GP = kWave / LPB;
+  static_assert(U <= LPB, "one lane per item of the batch");
+  __shared__ uint32_t tab_all[kWavesPerBlock][GP * U * LPB];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int grp = lane / LPB, gl = lane % LPB;
+  const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
+  if (wave * GP >= p.num_bags) return;  // whole wavefront
+  uint32_t* tab = tab_all[threadIdx.x >> 6] + grp * U * LPB;
+  const uint64_t g = wave * GP + grp;
+  const bool live = g < p.num_bags;
+  const RowLane<V, LPB> rl(p, gl);
+  const uint32_t jl = rl.jc - rl.j0;
+  int64_t e = 0, e1 = 0;
+  uint32_t t = 0, b = 0;
+  if (live) {
+    e = offset_at(offsets, g, p.idx32);
+    e1 = offset_at(offsets, g + 1, p.idx32);
+    e = e < 0 ? 0 : (e > p.N ? p.N : e);
+    e1 = e1 < 0 ? 0 : (e1 > p.N ? p.N : e1);
+    if (e1 < e) e1 = e;
+    t = static_cast<uint32_t>(g) / p.B;  // bags number fewer than 2^32
+    b = static_cast<uint32_t>(g) - t * p.B;
+  }
+  const uint32_t tC = t * p.C;
+  uint32_t left = static_cast<uint32_t>(e1 - e);  // N < 2^32
+  const uint32_t len = left;
+  typename Piece<V>::type acc = {};
+  uint32_t ix = 0;
+  if (gl < U && static_cast<uint32_t>(gl) < left)
+    ix = index_at(indices, static_cast<uint64_t>(e + gl), p.idx32);
+  while (__ballot(left != 0)) {
+    const uint32_t n = left < U ? left : U;
+    const uint32_t h0 = item_hash(ix, tC, p.TC, p.a, p.b);
+    if (gl < U && static_cast<uint32_t>(U + gl) < left)
+      ix = index_at(indices, static_cast<uint64_t>(e + U + gl), p.idx32);
+#pragma unroll 1
+    for (uint32_t k0 = 0; __ballot(k0 < n * rl.Cs); k0 += LPB) {
+      const uint32_t k = k0 + gl;
+      const uint32_t i = k / rl.Cs, j = k - i * rl.Cs;
+      const uint32_t h = __shfl(h0, grp * LPB + static_cast<int>(i < U ? i : 0u));
+      if (k < n * rl.Cs) tab[k] = item_entry<SIGN>(p, h, rl.j0 + j);
+    }
+    table_fence();
+    uint32_t ent[U];
+    bool split = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      // past the bag's end: its last item again (element 0 for an empty bag)
+      const uint32_t uu = static_cast<uint32_t>(u) < n ? u : (n ? n - 1 : 0u);
+      ent[u] = n ? tab[uu * rl.Cs + jl] : 0u;
+      split |= n && splits<V, SIGN>(ent[u], rl.kk, p.M);
+    }
+    if (__ballot(split)) {  // a piece runs past the end of the array
+#pragma unroll 1
+      for (uint32_t u = 0; u < n; ++u) {
+        const uint32_t en = tab[u * rl.Cs + jl];
+        acc += sign_piece<SIGN>(gather_split<WT, V, SIGN>(w, en, rl.kk, p.M), en);
+      }
+    } else {
+      typename Piece<V>::type v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = gather<WT, V, SIGN>(w, ent[u], n ? rl.kk : 0u, p.M);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (static_cast<uint32_t>(u) < n) acc += sign_piece<SIGN>(v[u], ent[u]);
+    }
+    table_fence();
+    e += n;
+    left -= n;
+  }
+  if (p.mean && len) acc /= static_cast<float>(len);
+  if (live && rl.act)
+    store_piece(out, static_cast<uint64_t>(b) * p.row_stride + static_cast<uint64_t>(t) * p.d + rl.c,
+                acc, p.rows_bf16);
+}
+
+// As many items as bags (N == T*B), usually one per bag: a wavefront takes NB = U * GP
+// consecutive bags, a lane each for the index and item hash, then gathers and stores U
+// pieces per lane.  A wavefront that meets a bag of another length or position, or a
+// piece split by the end of the array, works bag by bag.
+//
+// This replaced a persistent kernel that wrote the output in row order, one
+// wavefront per SIMD in groups of 32 steps: 3328 rows of 512 bytes 11.8 -> 4.2 us, 10240
+// 13 -> 5 us, 26 x 2048 13.1 -> 9 us, 26 x 16384 50.7 -> 45.4 us, 26 x 65536
+// 179 -> 170 us (187 -> 176 us in a training step); and the tiled kernel for d = 16 and
+// 1024 rows 18.1 -> 4.0 us.  Writing the rows alone in table order takes 160-170 us at
+// 26 x 65536 (5.1-5.4 TB/s); small batches are bound by the chain of
+// index load, hash, gather and store.
+template <typename WT, int V, int LPB, bool SIGN>
+__global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
+    const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
+    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t touch_blocks) {
+  constexpr int U = row_batch<V, LPB>();
+  constexpr int GP = kWave / LPB;
+  constexpr int NB = U * GP;
+  static_assert(NB <= kWave, "one lane per bag");
+  touch_batch(p, indices, offsets, out, touch_blocks);
+  __shared__ uint32_t tab_all[kWavesPerBlock][NB * LPB];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int grp = lane / LPB, gl = lane % LPB;
+  const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
+  const uint64_t q0 = wave * NB;
+  if (q0 >= p.num_bags) return;  // whole wavefront
+  uint32_t* tab = tab_all[threadIdx.x >> 6];
+  const uint32_t nb = p.num_bags - q0 < NB ? static_cast<uint32_t>(p.num_bags - q0) : NB;
+  const bool mine = static_cast<uint32_t>(lane) < nb;
+  const uint32_t g = static_cast<uint32_t>(q0) + (mine ? lane : 0u);  // bags number below 2^32
+  const uint32_t t = g / p.B, b = g - t * p.B;
+  const int64_t o0 = offset_at(offsets, g, p.idx32);
+  const int64_t o1 = offset_at(offsets, static_cast<uint64_t>(g) + 1, p.idx32);
+  const uint32_t idx = index_at(indices, g, p.idx32);  // g < N
+  const RowLane<V, LPB> rl(p, gl);
+  const uint32_t jl = rl.jc - rl.j0;
+  const uint32_t tC = t * p.C;
+  const uint64_t ro = static_cast<uint64_t>(b) * p.row_stride + static_cast<uint64_t>(t) * p.d;
+  const uint32_t h0 = item_hash(idx, tC, p.TC, p.a, p.b);
+#pragma unroll 1
+  for (uint32_t k0 = 0; k0 < nb * rl.Cs; k0 += kWave) {
+    const uint32_t k = k0 + lane;
+    const uint32_t i = k / rl.Cs, j = k - i * rl.Cs;
+    const uint32_t h = __shfl(h0, static_cast<int>(i < NB ? i : 0u));
+    if (k < nb * rl.Cs) tab[k] = item_entry<SIGN>(p, h, rl.j0 + j);
+  }
+  table_fence();
+  uint32_t ent[U];
+  bool odd = mine && !(o0 == static_cast<int64_t>(g) && o1 == static_cast<int64_t>(g) + 1);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t i = static_cast<uint32_t>(u * GP + grp);
+    ent[u] = tab[(i < nb ? i : 0u) * rl.Cs + jl];
+    odd |= splits<V, SIGN>(ent[u], rl.kk, p.M);
+  }
+  if (__ballot(odd)) {
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+      const int i = u * GP + grp;
+      const int64_t s0 = __shfl(o0, i), s1 = __shfl(o1, i);
+      const uint32_t tCi = __shfl(tC, i);
+      const uint64_t roi = __shfl(ro, i);
+      if (static_cast<uint32_t>(i) >= nb) continue;
+      const int64_t f0 = s0 < 0 ? 0 : (s0 > p.N ? p.N : s0);
+      int64_t f1 = s1 < 0 ? 0 : (s1 > p.N ? p.N : s1);
+      if (f1 < f0) f1 = f0;
+      typename Piece<V>::type acc = {};
+#pragma unroll 1
+      for (int64_t e = f0; e < f1; ++e) {
+        const uint32_t h =
+            item_hash(index_at(indices, static_cast<uint64_t>(e), p.idx32), tCi, p.TC, p.a, p.b);
+        const uint32_t en = item_entry<SIGN>(p, h, rl.jc);
+        acc += sign_piece<SIGN>(gather_split<WT, V, SIGN>(w, en, rl.kk, p.M), en);
+      }
+      if (p.mean && f1 > f0) acc /= static_cast<float>(f1 - f0);
+      if (rl.act) store_piece(out, roi + rl.c, acc, p.rows_bf16);
+    }
+    return;
+  }
+  typename Piece<V>::type v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) v[u] = gather<WT, V, SIGN>(w, ent[u], rl.kk, p.M);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = u * GP + grp;
+    const uint64_t roi = __shfl(ro, i);
+    if (static_cast<uint32_t>(i) < nb && rl.act)
+      store_piece(out, roi + rl.c, sign_piece<SIGN>(v[u], ent[u]), p.rows_bf16);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Tiled: one wavefront per tile of 64 bags of one table.  Each lane evaluates
+// the C <= kTabChunks chunk bases of one item of the current 64-item block into a
+// wave-private LDS table and the gathers read their base from it.  U items
+// are gathered before any is consumed, and all U gathers of a batch are
+// issued before any store of that batch (on gfx9 stores and loads share one
+// in-order wait counter).
+// ---------------------------------------------------------------------------
 
 // One-hot tile: item l of the tile is bag l.  The (h0, bag) pairs are sorted
 // across the lanes; every run of equal h0 is one token, gathered once (U runs
@@ -99,35 +477,27 @@ __device__ __forceinline__ void forward_onehot_tile(
         const uint64_t ro = readlane_u64(tl.row_off, b) + c0 + lane;
 #pragma unroll
         for (int r = 0; r < EPL; ++r)
-          if (act[r]) store_out(out, ro + kWave * r, v[u][r], p.rows_bf16);
+          if (act[r]) store_piece(out, ro + kWave * r, v[u][r], p.rows_bf16);
       }
     }
   }
 }
 
-template <typename WT, int EPL, int U, bool TAB, bool SIGN>
+template <typename WT, int EPL, int U, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t xcd_split) {
+    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t touch_blocks) {
+  touch_batch(p, indices, offsets, out, touch_blocks);
   const int lane = threadIdx.x & (kWave - 1);
-  // Workgroups are dispatched round-robin over the chip's XCDs (workgroup b
-  // on XCD b mod kXcds), each with an L2 of its own.  Tiles are table-major,
-  // so with xcd_split XCD x takes a contiguous share of the tiles and its L2
-  // holds the hot tokens of about 1/kXcds of the tables (grid.x is then a
-  // multiple of kXcds; any other dispatch order only changes which L2 sees
-  // which tile).
-  const uint64_t per_xcd = gridDim.x / kXcds;
-  const uint64_t blk =
-      xcd_split ? (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds : blockIdx.x;
-  const uint64_t wave = blk * kWavesPerBlock + (threadIdx.x >> 6);
+  const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
   const uint64_t g0 = wave * kTileBags;
   if (g0 >= p.num_bags) return;
   const uint32_t c0 = blockIdx.y * (kWave * EPL);
 
-  __shared__ uint32_t tab_all[TAB ? kWavesPerBlock * kWave * kTabStride : 1];
-  uint32_t* tab = tab_all + (TAB ? (threadIdx.x >> 6) * kWave * kTabStride : 0);
+  __shared__ uint32_t tab_all[kWavesPerBlock * kWave * kTabStride];
+  uint32_t* tab = tab_all + (threadIdx.x >> 6) * kWave * kTabStride;
 
-  uint32_t step[EPL], step2[EPL], kk[EPL], jj[EPL];
+  uint32_t kk[EPL], jj[EPL];
   bool act[EPL];
 #pragma unroll
   for (int r = 0; r < EPL; ++r) {
@@ -136,23 +506,19 @@ __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
     const uint32_t cc = act[r] ? c : 0;
     jj[r] = cc / p.Z;
     kk[r] = cc - jj[r] * p.Z;
-    step[r] = TAB ? 0u : chunk_step(p.a, jj[r]);
-    step2[r] = (TAB || !SIGN) ? 0u : chunk_step(p.a2, jj[r]);
   }
 
   // One-hot batches: item g0 + lane is usually bag g0 + lane's item; its
   // index is requested together with the offsets.
   uint32_t spec = 0;
-  if (TAB && static_cast<int64_t>(g0) + lane < p.N) spec = load_index(indices, g0 + lane, p.idx32);
+  if (static_cast<int64_t>(g0) + lane < p.N) spec = load_index(indices, g0 + lane, p.idx32);
   const Tile tl = load_tile(p, offsets, g0, lane);
 
-  if (TAB) {
-    // One-hot tile (every bag exactly one item): gather each distinct token
-    // of the tile once and store its row to every bag that reads it.
-    if (__ballot(lane >= tl.nb || tl.len == 1) == ~0ull) {
-      forward_onehot_tile<WT, EPL, U, SIGN>(w, p, tl, indices, out, tab, lane, c0, jj, kk, act, spec);
-      return;
-    }
+  // One-hot tile (every bag exactly one item): gather each distinct token
+  // of the tile once and store its row to every bag that reads it.
+  if (__ballot(lane >= tl.nb || tl.len == 1) == ~0ull) {
+    forward_onehot_tile<WT, EPL, U, SIGN>(w, p, tl, indices, out, tab, lane, c0, jj, kk, act, spec);
+    return;
   }
 
   float acc[EPL];
@@ -168,7 +534,7 @@ __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
     for (int r = 0; r < EPL; ++r) {
       if (act[r]) {
         const float x = zero ? 0.f : (p.mean ? acc[r] / div : acc[r]);
-        store_out(out, ro + kWave * r, x, p.rows_bf16);
+        store_piece(out, ro + kWave * r, x, p.rows_bf16);
       }
     }
   };
@@ -181,7 +547,7 @@ __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
     if (lane < n) idx = load_index(indices, e, p.idx32);
     const int bag = bag_of_item(tl, e);
     const uint32_t tC = __shfl(tl.tC, bag);
-    if (TAB) fill_base_table<SIGN>(tab, item_hash(idx, tC, p.TC, p.a, p.b), p, lane);
+    fill_base_table<SIGN>(tab, item_hash(idx, tC, p.TC, p.a, p.b), p, lane);
 
     for (int q = 0; q < n; q += U) {
       // Gather phase: straight-line, U items x EPL loads in flight.  Items
@@ -191,17 +557,9 @@ __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int uu = q + u < n ? q + u : n - 1;
-        uint32_t h0 = 0, h20 = 0;
-        if (!TAB) {
-          h0 = item_hash(readlane_u32(idx, uu), readlane_u32(tC, uu), p.TC, p.a, p.b);
-          if (SIGN) h20 = sign_hash0(h0, p.s_alpha, p.s_beta);
-        }
 #pragma unroll
         for (int r = 0; r < EPL; ++r) {
-          const uint32_t ent =
-              TAB ? tab[uu * kTabStride + jj[r]]
-                  : chunk_entry<SIGN>(fast_mod(add_mod_p(h0, step[r]), p.fm_c, p.M),
-                                      add_mod_p(h20, step2[r]), p);
+          const uint32_t ent = tab[uu * kTabStride + jj[r]];
           const Elem el = elem_of<SIGN>(ent, kk[r], p.M);
           const float x = load_weight(w, act[r] ? el.m : 0u);
           v[u][r] = SIGN ? apply_sign(x, el) : x;
@@ -230,504 +588,102 @@ __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
   for (int z = cur + 1; z < tl.nb; ++z) store_row(z, true);
 }
 
-// ---------------------------------------------------------------------------
-// Streamed forward for batches with one item per bag.
-//
-// HBM takes writes fastest when the stores in flight across the chip cover a
-// narrow window of addresses that advances through the array; the tiled
-// kernel above writes 512-byte row pieces spread over the whole output.  Here
-// a persistent grid of one wavefront per SIMD writes the output in row order:
-// at step s every wavefront stores one 1 KB unit (64 lanes x 4 elements: PPU =
-// 256/d row pieces of d elements), and the units of one step lie within about
-// 1 MB of rows.  Each lane gathers its 4 elements with one 16-byte load (a
-// chunk of Z % 4 == 0 elements never splits a lane's 4 elements).
-//
-// Which pieces a wavefront takes (StreamMap): each XCD (workgroups are
-// dispatched round-robin over the XCDs) owns a fixed share of the tables, so
-// that its L2 holds the hot tokens of a few tables instead of all of them,
-// while every XCD walks the rows at the same pace.
-//
-// Pipelining (loads and stores share one in-order wait counter on gfx9): a
-// wavefront works in groups of D steps (32 for d >= 128, using all 64 lanes
-// for the group's bags).  Three item sets rotate: while group n is stored and
-// group n + 1 gathered, the offsets and index of group n + 3 are requested, so
-// neither the index loads nor the gathers wait for a recent store.  Index and
-// offset loads are ordinary (cached) loads: one 64-byte line of indices serves
-// 8 rows of a table, which wavefronts of the same XCD read at about the same
-// time.
-//
-// A bag that is not exactly one item at position offsets[g] == g (an empty
-// bag, a bag of several items, or a permuted layout) is pooled by a slow path
-// that walks its items; the fast path applies to every bag of a one-hot batch.
-// ---------------------------------------------------------------------------
-// Steps per group: D * PPU bags fit one wavefront's lanes.
-template <int PPU> constexpr int stream_group() { return PPU >= 4 ? 16 : 32; }
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // 4-byte aligned
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-struct StreamItems {
-  uint32_t idx;      // index of the bag's (speculated) item
-  int64_t o0, o1;    // offsets[g], offsets[g + 1]
-  uint32_t g;        // bag
-  uint32_t t;        // its table
-  uint32_t o4;       // first element of its row piece in out, / 4
-  bool valid;        // lane holds a bag of the batch
-};
-
-// Placement of row pieces: the XCD groups (8 when the grid is a multiple of
-// 8, else 1) each take a fixed share of the tables.  Rows go in periods of L
-// rows (T*L divisible by the group count); the T*L pieces of a period, in
-// table-major order, are split into equal runs of K, one run per group, so a
-// group meets the same few tables throughout while all groups advance
-// through the rows together.
-struct StreamMap {
-  uint32_t nw;   // wavefronts of this XCD group
-  uint32_t w;    // this wavefront's rank in the group
-  uint32_t x;    // the group
-  uint32_t L;    // rows per period
-  uint32_t K;    // pieces per group and period
-  uint64_t Kx;   // pieces of the group: K * ceil(B / L)
-};
-
-template <bool I32>
-__device__ __forceinline__ uint32_t load_index_cached(const void* idx, uint64_t e) {
-  if constexpr (I32) return static_cast<uint32_t>(static_cast<const int32_t*>(idx)[e]);
-  else return static_cast<uint32_t>(static_cast<const int64_t*>(idx)[e]);
-}
-template <bool I32>
-__device__ __forceinline__ int64_t load_offset_cached(const void* off, uint64_t g) {
-  if constexpr (I32) return static_cast<int64_t>(static_cast<const int32_t*>(off)[g]);
-  else return static_cast<const int64_t*>(off)[g];
+// Workgroups of a grid over `waves` wavefronts: a multiple of kXcds (the
+// extra workgroups lie past the last bag and exit at once); 0 = too many.
+static uint32_t grid_of(uint64_t waves) {
+  const uint64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+  const uint64_t grid = (blocks + kXcds - 1) / kXcds * kXcds;
+  return grid > 0x7fffffffull ? 0u : static_cast<uint32_t>(grid);
 }
 
-// Lane i < D * PPU requests the bag of group n's step i / PPU, row piece
-// i % PPU of that step's unit.  Bags, and so row pieces, number fewer than
-// 2^32; its piece's first output element is below 2^34 (o4 fits 32 bits).
-template <int PPU, bool I32>
-__device__ __forceinline__ void stream_items(StreamItems& it, const KParams& p,
-                                             const void* __restrict__ indices,
-                                             const void* __restrict__ offsets, uint64_t n,
-                                             const StreamMap& sm, int lane) {
-  constexpr int D = stream_group<PPU>();
-  const uint64_t unit = (n * D + static_cast<uint64_t>(lane / PPU)) * sm.nw + sm.w;
-  const uint64_t piece = unit * PPU + static_cast<uint64_t>(lane % PPU);
-  bool valid = lane < D * PPU && piece < sm.Kx;
-  const uint32_t pc = valid ? static_cast<uint32_t>(piece) : 0u;  // Kx < 2^32
-  const uint32_t Q = pc / sm.K, k = pc - Q * sm.K;
-  const uint32_t q = sm.x * sm.K + k;  // < T * L
-  const uint32_t tq = q / sm.L;
-  const uint32_t r = Q * sm.L + (q - tq * sm.L);
-  valid = valid && r < p.B;
-  it.valid = valid;
-  it.t = valid ? tq : 0u;
-  const uint32_t rr = valid ? r : 0u;
-  it.g = it.t * p.B + rr;  // < T*B <= 2^32 - 1
-  it.o4 = static_cast<uint32_t>(
-      (static_cast<uint64_t>(rr) * p.row_stride + static_cast<uint64_t>(it.t) * p.d) >> 2);
-  // out-of-batch lanes read bag 0 (offsets has T*B + 1 >= 2 entries)
-  const uint32_t g = it.g;
-  it.o0 = load_offset_cached<I32>(offsets, g);
-  it.o1 = load_offset_cached<I32>(offsets, static_cast<uint64_t>(g) + 1);
-  // the index of item g, which is the bag's item in a one-hot layout
-  const uint64_t e = static_cast<int64_t>(g) < p.N ? g : 0u;
-  it.idx = p.N > 0 ? load_index_cached<I32>(indices, e) : 0u;
+static bool one_per_bag(const KParams& p) { return static_cast<uint64_t>(p.N) == p.num_bags; }
+
+template <typename WT, int EPL, int U, bool SIGN>
+static hipError_t launch_tiled_t(const WT* w, const KParams& p, const void* indices,
+                                 const void* offsets, void* out, hipStream_t stream,
+                                 uint32_t touch) {
+  const uint32_t blocks = grid_of((p.num_bags + kTileBags - 1) / kTileBags);
+  if (blocks == 0) return hipErrorInvalidConfiguration;
+  const dim3 grid(blocks, (p.d + kWave * EPL - 1) / (kWave * EPL));
+  hipLaunchKernelGGL((forward_kernel<WT, EPL, U, SIGN>), grid, dim3(kBlockThreads), 0, stream, w,
+                     p, indices, offsets, out, touch);
+  return hipGetLastError();
 }
 
-// Elements kk .. kk+3 of the chunk of table entry `ent` (a chunk base, with
-// the sign bits of chunk_entry when SIGN), widened to float and signed.  One
-// 16-byte load (4-byte aligned) unless the 4 elements run past the end of
-// the array, where each wraps on its own.
 template <typename WT, bool SIGN>
-__device__ __forceinline__ f32x4 gather4(const WT* __restrict__ w, uint32_t ent, uint32_t kk,
-                                         uint32_t M) {
-  bool read = true;
-  uint32_t neg = 0, base = ent;
-  if (SIGN) {
-    read = ent != kSkip;
-    neg = ent & 0x80000000u;
-    base = read ? ent & 0x7fffffffu : 0u;
-  }
-  const uint32_t m = base + kk;  // < 2M <= 2^32
-  const bool wrap = m + 3 >= M;
-  const uint32_t mv = wrap ? 0u : m;  // M >= Z >= 4: elements 0..3 exist
-  f32x4 x;
-  if constexpr (sizeof(WT) == 4) {
-    x = *reinterpret_cast<const f32x4u*>(reinterpret_cast<const float*>(w) + mv);
-  } else {
-    x = f32x4{load_weight(w, mv), load_weight(w, mv + 1), load_weight(w, mv + 2),
-              load_weight(w, mv + 3)};
-  }
-  if (wrap) {
-    x = f32x4{load_weight(w, wrap_add(base, kk, M)), load_weight(w, wrap_add(base, kk + 1, M)),
-              load_weight(w, wrap_add(base, kk + 2, M)), load_weight(w, wrap_add(base, kk + 3, M))};
-  }
-  if (SIGN) {
-    if (!read) return f32x4{0.f, 0.f, 0.f, 0.f};
-    x = f32x4{__uint_as_float(__float_as_uint(x.x) ^ neg), __uint_as_float(__float_as_uint(x.y) ^ neg),
-              __uint_as_float(__float_as_uint(x.z) ^ neg), __uint_as_float(__float_as_uint(x.w) ^ neg)};
-  }
-  return x;
+static hipError_t launch_tiled(const WT* w, const KParams& p, const void* indices,
+                               const void* offsets, void* out, hipStream_t stream,
+                               uint32_t touch) {
+  if (p.d <= 64) return launch_tiled_t<WT, 1, 16, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (p.d <= 128) return launch_tiled_t<WT, 2, 8, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (p.d <= 256) return launch_tiled_t<WT, 4, 4, SIGN>(w, p, indices, offsets, out, stream, touch);
+  return launch_tiled_t<WT, 8, 2, SIGN>(w, p, indices, offsets, out, stream, touch);
 }
 
-// Chunk entry, for the lane's chunk (hash steps stepj, step2j), of the item
-// whose item hash is h.
-template <bool SIGN>
-__device__ __forceinline__ uint32_t stream_entry(uint32_t h, uint32_t stepj, uint32_t step2j,
-                                                 const KParams& p) {
-  const uint32_t base = fast_mod(add_mod_p(h, stepj), p.fm_c, p.M);
-  if (!SIGN) return base;
-  return chunk_entry<SIGN>(base, add_mod_p(sign_hash0(h, p.s_alpha, p.s_beta), step2j), p);
-}
-
-// Item hash of the bag of step d, row piece pcl (hashed by lane d * PPU + pcl).
-template <int PPU>
-__device__ __forceinline__ uint32_t pick_hash(uint32_t h0, int d, uint32_t pcl) {
-  uint32_t h = readlane_u32(h0, d * PPU);
-#pragma unroll
-  for (int q = 1; q < PPU; ++q) {
-    const uint32_t hq = readlane_u32(h0, d * PPU + q);
-    h = pcl == static_cast<uint32_t>(q) ? hq : h;
-  }
-  return h;
-}
-
-__device__ __forceinline__ int64_t readlane_i64(int64_t v, int lane) {
-  const uint32_t lo = readlane_u32(static_cast<uint32_t>(v), lane);
-  const uint32_t hi = readlane_u32(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32), lane);
-  return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-template <typename WT, int PPU, bool SIGN, bool I32>
-__global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
-    const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t nx,
-    const KeygenOut kg) {
-  constexpr int D = stream_group<PPU>();
-  const int lane = threadIdx.x & (kWave - 1);
-  // Workgroups go round-robin to the XCDs (grid.x is a multiple of nx).
-  StreamMap sm;
-  sm.x = blockIdx.x % nx;
-  sm.nw = (gridDim.x / nx) * kWavesPerBlock;
-  sm.w = (blockIdx.x / nx) * kWavesPerBlock + (threadIdx.x >> 6);
-  sm.L = 1;
-  while ((p.T * sm.L) % nx != 0) ++sm.L;  // nx <= 8
-  sm.K = p.T * sm.L / nx;
-  sm.Kx = static_cast<uint64_t>(sm.K) * ((p.B + sm.L - 1) / sm.L);
-  const uint64_t units = (sm.Kx + PPU - 1) / PPU;
-  const uint64_t steps = (units + sm.nw - 1) / sm.nw;
-  const uint64_t groups = (steps + D - 1) / D;
-
-  // Prefetch.  Each group's index and offset entries (the contiguous range of
-  // its tables) are read once, in whole 16-byte pieces lying inside the
-  // arrays, before the loop: the loop's item loads then find them in the
-  // caches instead of sending scattered reads to HBM in the middle of the
-  // write stream.  In a training step (entries not cached after the
-  // backward) this took the headline forward from 189 to 171 us.
-  //
-  // With kg (the backward's grouping prepared by this forward), the same
-  // entries are read by the grouping's keygen instead (keygen_process: the
-  // (h0, row) pairs and the first radix pass's digit counts of every sort
-  // tile), which then serves as the prefetch.  XCD x's workgroups take the
-  // contiguous x-th eighth of the sort tiles, about the tables it owns.
-  uint32_t pf = 0;
-  __shared__ KeygenLds kg_lds;
-  if (kg.keys != nullptr) {
-    const uint32_t per_x = (kg.nblocks + nx - 1) / nx;
-    const uint32_t lo = sm.x * per_x;
-    const uint32_t hi = lo + per_x < kg.nblocks ? lo + per_x : kg.nblocks;
-    const uint32_t wgs = gridDim.x / nx, rank = blockIdx.x / nx;
-    // the next tile's entries are requested before the current tile is
-    // worked (two input sets take turns)
-    KeygenIn ka, kb;
-    uint32_t tile = lo + rank;
-    if (tile < hi) keygen_load<I32, false>(p, indices, offsets, tile, ka);
-    while (tile < hi) {
-      const uint32_t t2 = tile + wgs;
-      if (t2 < hi) keygen_load<I32, false>(p, indices, offsets, t2, kb);
-      keygen_process<I32, false>(p, offsets, kg.keys, kg.rows, kg.inv_len, kg.counts, kg.nblocks,
-                                 tile, ka, kg_lds);
-      if (t2 >= hi) break;
-      const uint32_t t3 = t2 + wgs;
-      if (t3 < hi) keygen_load<I32, false>(p, indices, offsets, t3, ka);
-      keygen_process<I32, false>(p, offsets, kg.keys, kg.rows, kg.inv_len, kg.counts, kg.nblocks,
-                                 t2, kb, kg_lds);
-      tile = t3;
-    }
-  } else {
-    const uint64_t t_lo = static_cast<uint64_t>(sm.x) * sm.K / sm.L;
-    const uint64_t t_hi = (static_cast<uint64_t>(sm.x + 1) * sm.K - 1) / sm.L + 1;  // <= T
-    const uint64_t g_lo = t_lo * p.B, g_hi = t_hi * p.B;
-    const uint64_t es = I32 ? 4 : 8;
-    auto touch = [&](const void* base, uint64_t n_entries) {
-      const uint64_t hi_e = g_hi < n_entries ? g_hi : n_entries;
-      if (g_lo >= hi_e) return;
-      const uint64_t a0 = reinterpret_cast<uint64_t>(base);
-      const uint64_t c_lo = (a0 + g_lo * es + 15) / 16, c_end = (a0 + hi_e * es) / 16;
-      // kPrefetchBatch 16-byte pieces per lane requested before any is used
-      constexpr int kPrefetchBatch = 16;
-      const uint64_t stride = static_cast<uint64_t>(sm.nw) * kWave;
-      for (uint64_t c0 = c_lo + static_cast<uint64_t>(sm.w) * kWave + lane; c0 < c_end;
-           c0 += kPrefetchBatch * stride) {
-        uint4 v4[kPrefetchBatch];
-#pragma unroll
-        for (int k = 0; k < kPrefetchBatch; ++k) {
-          const uint64_t c = c0 + k * stride;
-          v4[k] = c < c_end ? *reinterpret_cast<const uint4*>(c * 16) : uint4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int k = 0; k < kPrefetchBatch; ++k) pf ^= v4[k].x ^ v4[k].y ^ v4[k].z ^ v4[k].w;
-      }
-    };
-    touch(indices, static_cast<uint64_t>(p.N));
-    touch(offsets, p.num_bags + 1);
-  }
-
-  // lane's 4 elements: row piece pcl of the unit, dims c .. c+3 of it
-  constexpr uint32_t kLanesPerPiece = kWave / PPU;
-  const uint32_t pcl = static_cast<uint32_t>(lane) / kLanesPerPiece;
-  const uint32_t c = (static_cast<uint32_t>(lane) % kLanesPerPiece) * 4;
-  const uint32_t j = c / p.Z, kk = c - j * p.Z;
-  const uint32_t stepj = chunk_step(p.a, j);
-  const uint32_t step2j = SIGN ? chunk_step(p.a2, j) : 0u;
-
-  auto hash_of = [&](const StreamItems& it) -> uint32_t {
-    return item_hash(it.idx, it.t * p.C, p.TC, p.a, p.b);
-  };
-  // bags of a group that are not one item at position g
-  auto slow_of = [&](const StreamItems& it) -> uint64_t {
-    const bool fast = it.o0 == static_cast<int64_t>(it.g) &&
-                      it.o1 == static_cast<int64_t>(it.g) + 1 && static_cast<int64_t>(it.g) < p.N;
-    return __ballot(it.valid && !fast);
-  };
-  f32x4 v[D];
-  // Pools each listed bag of a group over its items (all lanes of its row
-  // piece), in place of the speculative gather.
-  auto fixup = [&](uint64_t slow, const StreamItems& it) {
-    while (slow) {
-      const int i = __builtin_ctzll(slow);
-      slow &= slow - 1;
-      const int64_t o0 = readlane_i64(it.o0, i), o1 = readlane_i64(it.o1, i);
-      const uint32_t tC = readlane_u32(it.t, i) * p.C;
-      const int64_t e0 = o0 < 0 ? 0 : (o0 > p.N ? p.N : o0);
-      int64_t e1 = o1 < 0 ? 0 : (o1 > p.N ? p.N : o1);
-      if (e1 < e0) e1 = e0;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int64_t e = e0; e < e1; ++e) {
-        const uint32_t h =
-            item_hash(load_index_cached<I32>(indices, static_cast<uint64_t>(e)), tC, p.TC, p.a, p.b);
-        acc += gather4<WT, SIGN>(w, stream_entry<SIGN>(h, stepj, step2j, p), kk, p.M);
-      }
-      if (p.mean && e1 > e0) acc /= static_cast<float>(e1 - e0);
-      const int si = i / PPU;
-      const uint32_t pi = static_cast<uint32_t>(i % PPU);
-#pragma unroll
-      for (int d = 0; d < D; ++d)
-        if (d == si && pcl == pi) v[d] = acc;
-    }
-  };
-  // Stores group n (in v; piece offsets o4n, valid pieces vm) and gathers
-  // group n + 1 (item hashes hn) into v.
-  auto store_gather = [&](uint32_t hn, uint32_t o4n, uint64_t vm) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const uint64_t e = static_cast<uint64_t>(pick_hash<PPU>(o4n, d, pcl)) * 4 + c;
-      if ((vm >> (d * PPU + pcl)) & 1u) {
-        if (p.rows_bf16) {
-          const u32x2 x = {static_cast<uint32_t>(f32_to_bf16_rne(v[d].x)) |
-                               (static_cast<uint32_t>(f32_to_bf16_rne(v[d].y)) << 16),
-                           static_cast<uint32_t>(f32_to_bf16_rne(v[d].z)) |
-                               (static_cast<uint32_t>(f32_to_bf16_rne(v[d].w)) << 16)};
-          __builtin_nontemporal_store(x, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(out) + e));
-        } else {
-          __builtin_nontemporal_store(v[d], reinterpret_cast<f32x4*>(static_cast<float*>(out) + e));
-        }
-      }
-      v[d] = gather4<WT, SIGN>(w, stream_entry<SIGN>(pick_hash<PPU>(hn, d, pcl), stepj, step2j, p),
-                               kk, p.M);
-    }
-  };
-
-  // Three item sets take turns (no register copies of values still loading):
-  // while group n is stored, one set holds group n's items (for the slow path
-  // and the store addresses), the next group n + 1's, which are hashed, and
-  // the third group n + 2's, still loading; then the first is refilled with
-  // group n + 3.
-  StreamItems A, B, C;
-  stream_items<PPU, I32>(A, p, indices, offsets, 0, sm, lane);
-  uint64_t slow = slow_of(A);
-  {
-    const uint32_t h = hash_of(A);
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-      v[d] = gather4<WT, SIGN>(w, stream_entry<SIGN>(pick_hash<PPU>(h, d, pcl), stepj, step2j, p),
-                               kk, p.M);
-  }
-  stream_items<PPU, I32>(B, p, indices, offsets, 1, sm, lane);
-  stream_items<PPU, I32>(C, p, indices, offsets, 2, sm, lane);
-  for (uint64_t n = 0; n < groups; n += 3) {
-    fixup(slow, A);
-    slow = slow_of(B);
-    uint32_t h = hash_of(B);
-    const uint32_t o4A = A.o4;
-    const uint64_t vmA = __ballot(A.valid);
-    stream_items<PPU, I32>(A, p, indices, offsets, n + 3, sm, lane);
-    store_gather(h, o4A, vmA);
-    if (n + 1 >= groups) break;
-    fixup(slow, B);
-    slow = slow_of(C);
-    h = hash_of(C);
-    const uint32_t o4B = B.o4;
-    const uint64_t vmB = __ballot(B.valid);
-    stream_items<PPU, I32>(B, p, indices, offsets, n + 4, sm, lane);
-    store_gather(h, o4B, vmB);
-    if (n + 2 >= groups) break;
-    fixup(slow, C);
-    slow = slow_of(A);
-    h = hash_of(A);
-    const uint32_t o4C = C.o4;
-    const uint64_t vmC = __ballot(C.valid);
-    stream_items<PPU, I32>(C, p, indices, offsets, n + 5, sm, lane);
-    store_gather(h, o4C, vmC);
-  }
-  // never true (N >= 0): keeps the prefetch loads
-  if (pf == 0x9e3779b9u && p.N < 0) static_cast<uint32_t*>(out)[lane] = pf;
-}
-
-// The streamed forward applies when the batch has as many items as bags
-// (every bag may then be one item; others take the slow path), a lane's 4
-// elements lie in one chunk (Z % 4 == 0) and a 256-element unit holds whole
-// row pieces (d in {64, 128, 256}).  It is used for shared arrays that fit
-// the chip's aggregate L2; larger arrays keep the tiled kernel, whose tiles
-// partition the tables over the XCDs.  Measured on the 26-table one-hot batch
-// (65 536 samples, d = 128, 10 MB array), per launch: 172 us after another
-// forward and 187 us in a training step, against 200 us for the tiled kernel
-// (which gathers each distinct token of a tile once, but writes at about
-// 5.1 TB/s in its pattern).
-template <typename WT>
-static bool stream_applies(const KParams& p) {
-  return static_cast<uint64_t>(p.N) == p.num_bags && p.Z % 4 == 0 &&
-         (p.d == 64 || p.d == 128 || p.d == 256) &&
-         static_cast<uint64_t>(p.M) * sizeof(WT) <= kXcdSplitBytes &&
-         p.num_bags * p.d < (1ull << 34);
-}
-
-// Compute units of each device, looked up once per device (callers may run
-// on several threads and devices).
-constexpr int kMaxDevices = 64;
-static std::atomic<int> g_cus[kMaxDevices];
-
-static int device_cus() {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
-    (void)hipGetLastError();
-    return 256;
-  }
-  int n = g_cus[dev].load(std::memory_order_relaxed);
-  if (n <= 0) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        n <= 0) {
-      (void)hipGetLastError();
-      n = 256;
-    }
-    g_cus[dev].store(n, std::memory_order_relaxed);
-  }
-  return n;
-}
-
-// Wavefronts of the streamed forward: one per SIMD (4 per compute unit).
-static uint32_t stream_blocks(uint64_t units) {
-  const uint64_t cus = static_cast<uint64_t>(device_cus());
-  const uint64_t want = (units + kWavesPerBlock - 1) / kWavesPerBlock;
-  uint64_t blocks = want < cus ? want : cus;
-  if (blocks >= kXcds) blocks = blocks / kXcds * kXcds;
-  return static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
-}
-
-template <typename WT, int PPU, bool SIGN>
-static hipError_t launch_stream_t(const WT* w, const KParams& p, const void* indices,
-                                  const void* offsets, void* out, hipStream_t stream,
-                                  const KeygenOut& kg) {
-  const uint64_t units = (p.num_bags * p.d + kWave * 4 - 1) / (kWave * 4);
-  const uint32_t blocks = stream_blocks(units);
-  const uint32_t nx = blocks % kXcds == 0 ? kXcds : 1u;
-  if (p.idx32)
-    hipLaunchKernelGGL((forward_stream_kernel<WT, PPU, SIGN, true>), dim3(blocks),
-                       dim3(kBlockThreads), 0, stream, w, p, indices, offsets, out, nx, kg);
+template <typename WT, int V, int LPB, bool SIGN>
+static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indices,
+                                const void* offsets, void* out, hipStream_t stream,
+                               uint32_t touch) {
+  const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? row_batch<V, LPB>() : 1);
+  const uint32_t blocks = grid_of((p.num_bags + per_wave - 1) / per_wave);
+  if (blocks == 0) return hipErrorInvalidConfiguration;
+  const dim3 grid(blocks, (p.d + LPB * V - 1) / (LPB * V));
+  if (one_per_bag(p))
+    hipLaunchKernelGGL((forward_stream_kernel<WT, V, LPB, SIGN>), grid, dim3(kBlockThreads), 0,
+                       stream, w, p, indices, offsets, out, touch);
   else
-    hipLaunchKernelGGL((forward_stream_kernel<WT, PPU, SIGN, false>), dim3(blocks),
-                       dim3(kBlockThreads), 0, stream, w, p, indices, offsets, out, nx, kg);
+    hipLaunchKernelGGL((forward_bags_kernel<WT, V, LPB, SIGN>), grid, dim3(kBlockThreads), 0,
+                       stream, w, p, indices, offsets, out);
   return hipGetLastError();
 }
 
-template <typename WT, bool SIGN>
-static hipError_t launch_stream_s(const WT* w, const KParams& p, const void* indices,
-                                  const void* offsets, void* out, hipStream_t stream,
-                                  const KeygenOut& kg) {
-  if (p.d == 64) return launch_stream_t<WT, 4, SIGN>(w, p, indices, offsets, out, stream, kg);
-  if (p.d == 128) return launch_stream_t<WT, 2, SIGN>(w, p, indices, offsets, out, stream, kg);
-  return launch_stream_t<WT, 1, SIGN>(w, p, indices, offsets, out, stream, kg);
+template <typename WT, int V, bool SIGN>
+static hipError_t launch_rows_v(const WT* w, const KParams& p, const void* indices,
+                                const void* offsets, void* out, hipStream_t stream,
+                               uint32_t touch) {
+  const uint32_t lanes = (p.d + V - 1) / V;
+  if (lanes <= 4) return launch_rows_t<WT, V, 4, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (lanes <= 8) return launch_rows_t<WT, V, 8, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (lanes <= 16) return launch_rows_t<WT, V, 16, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (lanes <= 32) return launch_rows_t<WT, V, 32, SIGN>(w, p, indices, offsets, out, stream, touch);
+  return launch_rows_t<WT, V, 64, SIGN>(w, p, indices, offsets, out, stream, touch);
 }
 
-template <typename WT, int EPL, int U, bool TAB, bool SIGN>
-static hipError_t launch_fwd_t(const WT* w, const KParams& p, const void* indices,
-                               const void* offsets, void* out, hipStream_t stream) {
-  const uint64_t tiles = (p.num_bags + kTileBags - 1) / kTileBags;
-  const uint64_t blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
-  const uint32_t slabs = (p.d + kWave * EPL - 1) / (kWave * EPL);
-  if (blocks > 0x7fffffffull - kXcds) return hipErrorInvalidConfiguration;
-  const uint32_t xcd_split = static_cast<uint64_t>(p.M) * sizeof(WT) > kXcdSplitBytes ? 1u : 0u;
-  // with the split, grid.x is rounded up to a multiple of kXcds (the extra
-  // workgroups' tiles lie past the last bag: they exit at once)
-  const uint64_t grid_x = xcd_split ? (blocks + kXcds - 1) / kXcds * kXcds : blocks;
-  dim3 grid(static_cast<uint32_t>(grid_x), slabs);
-  hipLaunchKernelGGL((forward_kernel<WT, EPL, U, TAB, SIGN>), grid, dim3(kBlockThreads), 0, stream,
-                     w, p, indices, offsets, out, xcd_split);
-  return hipGetLastError();
-}
-
-template <typename WT, bool TAB, bool SIGN>
-static hipError_t launch_fwd_c(const WT* w, const KParams& p, const void* indices,
-                               const void* offsets, void* out, hipStream_t stream) {
-  if (p.d <= 64) return launch_fwd_t<WT, 1, 16, TAB, SIGN>(w, p, indices, offsets, out, stream);
-  if (p.d <= 128) return launch_fwd_t<WT, 2, 8, TAB, SIGN>(w, p, indices, offsets, out, stream);
-  if (p.d <= 256) return launch_fwd_t<WT, 4, 4, TAB, SIGN>(w, p, indices, offsets, out, stream);
-  return launch_fwd_t<WT, 8, 2, TAB, SIGN>(w, p, indices, offsets, out, stream);
+// The tiled kernel is kept where gathering each distinct token of 64 bags
+// once pays for its longer chain: one-hot batches of 2^20 bags or more on an
+// array beyond the aggregate L2.  Measured on 26 tables of Zipf(1.2) tokens, d = Z =
+// 128, 128 MB bfloat16 array, rows / tiled: 2048 samples 8.2 / 23.7 us, 16384
+// 44.9 / 65.2 us, 65536 212 / 199 us, 262144 990 / 774 us.
+template <typename WT>
+static bool tiled_applies(const KParams& p) {
+  return one_per_bag(p) && p.num_bags >= (1ull << 20) &&
+         p.C <= static_cast<uint32_t>(kTabChunks) &&
+         static_cast<uint64_t>(p.M) * sizeof(WT) > kL2Bytes;
 }
 
 template <typename WT, bool SIGN>
 static hipError_t launch_fwd_s(const WT* w, const KParams& p, const void* indices,
-                               const void* offsets, void* out, hipStream_t stream) {
-  if (p.C <= static_cast<uint32_t>(kTabChunks))
-    return launch_fwd_c<WT, true, SIGN>(w, p, indices, offsets, out, stream);
-  return launch_fwd_c<WT, false, SIGN>(w, p, indices, offsets, out, stream);
+                               const void* offsets, void* out, hipStream_t stream,
+                               uint32_t touch) {
+  if (tiled_applies<WT>(p)) return launch_tiled<WT, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (p.Z % 4 == 0) return launch_rows_v<WT, 4, SIGN>(w, p, indices, offsets, out, stream, touch);
+  return launch_rows_v<WT, 1, SIGN>(w, p, indices, offsets, out, stream, touch);
 }
 
 template <typename WT>
 static hipError_t launch_fwd_w(const WT* w, const KParams& p, const void* indices,
                                const void* offsets, void* out, hipStream_t stream,
-                               const KeygenOut* kg) {
-  if (stream_applies<WT>(p)) {
-    const KeygenOut none{};
-    const KeygenOut& k = kg != nullptr ? *kg : none;
-    if (p.sign_mode) return launch_stream_s<WT, true>(w, p, indices, offsets, out, stream, k);
-    return launch_stream_s<WT, false>(w, p, indices, offsets, out, stream, k);
-  }
-  if (kg != nullptr) return hipErrorInvalidValue;  // only the streamed kernel writes a keygen
-  if (p.sign_mode) return launch_fwd_s<WT, true>(w, p, indices, offsets, out, stream);
-  return launch_fwd_s<WT, false>(w, p, indices, offsets, out, stream);
-}
-
-bool forward_streams(const KParams& p, bool bf16) {
-  return bf16 ? stream_applies<uint16_t>(p) : stream_applies<float>(p);
+                               uint32_t touch) {
+  if (p.sign_mode) return launch_fwd_s<WT, true>(w, p, indices, offsets, out, stream, touch);
+  return launch_fwd_s<WT, false>(w, p, indices, offsets, out, stream, touch);
 }
 
 hipError_t launch_forward(const void* w, bool bf16, const KParams& p, const void* indices,
-                          const void* offsets, void* out, hipStream_t stream,
-                          const KeygenOut* kg) {
+                          const void* offsets, void* out, hipStream_t stream, bool batch_read) {
+  const uint32_t touch = !batch_read && p.num_bags >= kTouchBags ? kTouchBlocks : 0u;
   if (bf16)
-    return launch_fwd_w(static_cast<const uint16_t*>(w), p, indices, offsets, out, stream, kg);
-  return launch_fwd_w(static_cast<const float*>(w), p, indices, offsets, out, stream, kg);
+    return launch_fwd_w(static_cast<const uint16_t*>(w), p, indices, offsets, out, stream, touch);
+  return launch_fwd_w(static_cast<const float*>(w), p, indices, offsets, out, stream, touch);
 }
 
 }  // namespace pss

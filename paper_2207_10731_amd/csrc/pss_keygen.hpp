@@ -1,7 +1,6 @@
 // Keygen of the sorted backward's grouping (paper Sec. 3, Alg. 1: lookups
 // with equal tokens are grouped before their gradient rows are summed),
-// shared by the grouping's own keygen kernel and by the streamed forward,
-// which can run it while it reads the batch's index and offset entries.
+// in item space, for batches with as many items as bags.
 //
 // For every item e of a sort tile (kSortTile consecutive items) it writes
 // the pair (h0, r): h0 = the item hash of (index, table), equal for equal
@@ -20,17 +19,14 @@ constexpr int kSortItemsPerLane = 8;
 constexpr int kSortTile = kBlockThreads * kSortItemsPerLane;  // keys per block
 constexpr int kWaveSortKeys = kWave * kSortItemsPerLane;       // keys per wave
 
-// indices[e] / offsets[g] with the integer width fixed at compile time;
-// NT: non-temporal (a stream read once), else cached.
-template <bool I32, bool NT = true>
+// indices[e] / offsets[g] with the integer width fixed at compile time.
+// Cached: with PSS_PREPARE_BACKWARD the forward kernel that follows reads
+// the same entries (non-temporal loads here took it from 172 to 258 us on
+// 26 x 65536 rows).
+template <bool I32>
 __device__ __forceinline__ int64_t load_int(const void* a, uint64_t i) {
-  if constexpr (I32) {
-    const int32_t* q = static_cast<const int32_t*>(a) + i;
-    return NT ? __builtin_nontemporal_load(q) : *q;
-  } else {
-    const int64_t* q = static_cast<const int64_t*>(a) + i;
-    return NT ? __builtin_nontemporal_load(q) : *q;
-  }
+  if constexpr (I32) return static_cast<const int32_t*>(a)[i];
+  else return static_cast<const int64_t*>(a)[i];
 }
 
 // LDS of keygen_process.
@@ -39,9 +35,7 @@ struct KeygenLds {
   int irregular;
 };
 
-// Inputs of one sort tile, requested ahead of their use (keygen_load), so
-// that a workgroup can ask for its next tile's entries before it works on
-// the current one.
+// Inputs of one sort tile, all requested before any is used (keygen_load).
 struct KeygenIn {
   uint32_t ix[kSortItemsPerLane];
   int64_t ofs[kSortItemsPerLane];
@@ -51,7 +45,7 @@ struct KeygenIn {
 // Requests the thread's indices and offsets of sort tile `tile` (items
 // [tile * kSortTile, ...)): every load is issued before any is used.  An
 // item's index does not depend on its bag.
-template <bool I32, bool NT>
+template <bool I32>
 __device__ __forceinline__ void keygen_load(const KParams& p, const void* __restrict__ indices,
                                             const void* __restrict__ offsets, const uint32_t tile,
                                             KeygenIn& in) {
@@ -66,12 +60,12 @@ __device__ __forceinline__ void keygen_load(const KParams& p, const void* __rest
     in.ix[s] = 0;
     in.ofs[s] = e;
     if (li < in_tile) {
-      in.ix[s] = static_cast<uint32_t>(load_int<I32, NT>(indices, static_cast<uint64_t>(e)));
-      in.ofs[s] = load_int<I32, NT>(offsets, static_cast<uint64_t>(e));
+      in.ix[s] = static_cast<uint32_t>(load_int<I32>(indices, static_cast<uint64_t>(e)));
+      in.ofs[s] = load_int<I32>(offsets, static_cast<uint64_t>(e));
     }
   }
   const int64_t end = tile0 + in_tile;
-  in.oend = threadIdx.x == 0 ? load_int<I32, NT>(offsets, static_cast<uint64_t>(end)) : end;
+  in.oend = threadIdx.x == 0 ? load_int<I32>(offsets, static_cast<uint64_t>(end)) : end;
 }
 
 // Keygen of sort tile `tile` in item space, for batches with as many items
@@ -82,7 +76,7 @@ __device__ __forceinline__ void keygen_load(const KParams& p, const void* __rest
 // search over the offsets (the largest g with offsets[g] <= e).  With mean
 // pooling it also writes inv_len[r] = 1 / |bag| for the row of every
 // nonempty bag whose first item lies in the tile.
-template <bool I32, bool NT>
+template <bool I32>
 __device__ __forceinline__ void keygen_process(const KParams& p, const void* __restrict__ offsets,
                                                uint32_t* __restrict__ keys,
                                                uint32_t* __restrict__ rows,
@@ -95,7 +89,6 @@ __device__ __forceinline__ void keygen_process(const KParams& p, const void* __r
   const int w = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
   const int lbase = w * kWaveSortKeys;
   const int64_t end = tile0 + in_tile;
-  __syncthreads();  // a previous tile of this workgroup is done with the LDS
   for (int i = threadIdx.x; i < kWavesPerBlock * kBins; i += kBlockThreads)
     (&lds.hist[0][0])[i] = 0;
   if (threadIdx.x == 0) lds.irregular = 0;
@@ -122,11 +115,11 @@ __device__ __forceinline__ void keygen_process(const KParams& p, const void* __r
         uint64_t lo = 0, hi = p.num_bags - 1;  // largest g with offsets[g] <= e
         while (lo < hi) {
           const uint64_t mid = (lo + hi + 1) >> 1;
-          if (load_int<I32, NT>(offsets, mid) <= e) lo = mid; else hi = mid - 1;
+          if (load_int<I32>(offsets, mid) <= e) lo = mid; else hi = mid - 1;
         }
         g = static_cast<uint32_t>(lo);
-        const int64_t s0 = load_int<I32, NT>(offsets, lo);
-        const int64_t s1 = load_int<I32, NT>(offsets, lo + 1);
+        const int64_t s0 = load_int<I32>(offsets, lo);
+        const int64_t s1 = load_int<I32>(offsets, lo + 1);
         first = s0 == e;
         il = s1 > s0 ? 1.f / static_cast<float>(s1 - s0) : 1.f;
       }

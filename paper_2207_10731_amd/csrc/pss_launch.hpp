@@ -9,8 +9,7 @@
 namespace pss {
 
 // First stage of the grouping (keys, rows, the first radix pass's digit
-// counts, inv_len with mean pooling) as laid out in its workspace; the
-// streamed forward can write it (keys == nullptr: not requested).
+// counts, inv_len with mean pooling) as laid out in its workspace.
 struct KeygenOut {
   uint32_t* keys = nullptr;
   uint32_t* rows = nullptr;
@@ -20,13 +19,10 @@ struct KeygenOut {
 };
 // Forward: pooled rows of every bag into out[B][T*d].
 // indices / offsets are int64 (int32 when p.idx32); out / grad rows are
-// float32 (bfloat16 when p.rows_bf16).  With kg (streamed kernel only, see
-// forward_streams) the kernel also writes the grouping's first stage there.
+// float32 (bfloat16 when p.rows_bf16).  batch_read: the work just enqueued on
+// the stream has read indices and offsets (they are in the caches).
 hipError_t launch_forward(const void* w, bool bf16, const KParams& p, const void* indices,
-                          const void* offsets, void* out, hipStream_t stream,
-                          const KeygenOut* kg = nullptr);
-// Whether the forward of this batch runs the streamed kernel.
-bool forward_streams(const KParams& p, bool bf16);
+                          const void* offsets, void* out, hipStream_t stream, bool batch_read);
 
 // Atomic deposit: dst[addr] += scale * grad for every (item, dim).
 hipError_t launch_deposit_atomic(float* dst, float scale, const KParams& p, const void* indices,
@@ -49,6 +45,11 @@ struct GroupedPairs {
   const float* inv_len = nullptr;  // 1 / |bag| per pooled row (mean pooling)
 };
 KeygenOut keygen_layout(const KParams& p, void* workspace);
+// The first stage in item space, digit counts included: batches with as
+// many items as bags (keygen_counts).
+bool keygen_counts(const KParams& p);
+hipError_t launch_keygen_counts(const KParams& p, const void* indices, const void* offsets,
+                                const KeygenOut& kg, hipStream_t stream);
 // The rest of the grouping once its first stage is in the workspace
 // (first_counted: the first pass's digit counts are there too).
 hipError_t finish_group_sorted(const KParams& p, void* workspace, bool first_counted,

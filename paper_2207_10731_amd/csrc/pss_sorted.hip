@@ -184,8 +184,8 @@ __global__ __launch_bounds__(kBlockThreads) void keygen_hist_kernel(
   if (tile >= nblocks) return;
   __shared__ KeygenLds lds;
   KeygenIn in;
-  keygen_load<I32, true>(p, indices, offsets, tile, in);
-  keygen_process<I32, true>(p, offsets, keys, rows, inv_len, counts, nblocks, tile, in, lds);
+  keygen_load<I32>(p, indices, offsets, tile, in);
+  keygen_process<I32>(p, offsets, keys, rows, inv_len, counts, nblocks, tile, in, lds);
 }
 
 // Scans of the count rows.  A chunk of kScanChunk consecutive entries is
@@ -938,32 +938,33 @@ hipError_t finish_group_sorted(const KParams& p, void* workspace, bool first_cou
   return e;
 }
 
+bool keygen_counts(const KParams& p) { return static_cast<uint64_t>(p.N) == p.num_bags; }
+
+hipError_t launch_keygen_counts(const KParams& p, const void* indices, const void* offsets,
+                                const KeygenOut& kg, hipStream_t stream) {
+  const uint32_t per_xcd = sort_tiles_per_xcd(kg.nblocks);
+  const dim3 grid(per_xcd * static_cast<uint32_t>(kXcds));
+  if (p.idx32)
+    hipLaunchKernelGGL(keygen_hist_kernel<true>, grid, dim3(kBlockThreads), 0, stream, p, indices,
+                       offsets, kg.keys, kg.rows, kg.inv_len, kg.counts, kg.nblocks, per_xcd);
+  else
+    hipLaunchKernelGGL(keygen_hist_kernel<false>, grid, dim3(kBlockThreads), 0, stream, p, indices,
+                       offsets, kg.keys, kg.rows, kg.inv_len, kg.counts, kg.nblocks, per_xcd);
+  return hipGetLastError();
+}
+
 hipError_t launch_group_sorted(const KParams& p, const void* indices, const void* offsets,
                                void* workspace, hipStream_t stream, GroupedPairs* out) {
-  const int64_t N = p.N;
   const KeygenOut kg = keygen_layout(p, workspace);
-  if (N == 0) return finish_group_sorted(p, workspace, false, stream, out);
+  if (p.N == 0) return finish_group_sorted(p, workspace, false, stream, out);
   // As many items as bags (one-hot batches): keygen in item space, fused
   // with the first pass's histogram.
-  const bool item_space = static_cast<uint64_t>(N) == p.num_bags;
-  hipError_t e = hipSuccess;
-  if (item_space) {
-    const uint32_t per_xcd = sort_tiles_per_xcd(kg.nblocks);
-    const dim3 grid(per_xcd * static_cast<uint32_t>(kXcds));
-    if (p.idx32)
-      hipLaunchKernelGGL(keygen_hist_kernel<true>, grid, dim3(kBlockThreads), 0, stream, p,
-                         indices, offsets, kg.keys, kg.rows, kg.inv_len, kg.counts, kg.nblocks,
-                         per_xcd);
-    else
-      hipLaunchKernelGGL(keygen_hist_kernel<false>, grid, dim3(kBlockThreads), 0, stream, p,
-                         indices, offsets, kg.keys, kg.rows, kg.inv_len, kg.counts, kg.nblocks,
-                         per_xcd);
-    e = hipGetLastError();
-  } else {
-    e = launch_keygen(p, indices, offsets, kg.keys, kg.rows, kg.inv_len, stream);
-  }
+  const bool counted = keygen_counts(p);
+  const hipError_t e =
+      counted ? launch_keygen_counts(p, indices, offsets, kg, stream)
+              : launch_keygen(p, indices, offsets, kg.keys, kg.rows, kg.inv_len, stream);
   if (e != hipSuccess) return e;
-  return finish_group_sorted(p, workspace, item_space, stream, out);
+  return finish_group_sorted(p, workspace, counted, stream, out);
 }
 
 hipError_t launch_reduce_sorted(float* dst, float scale, const KParams& p, const GroupedPairs& g,
