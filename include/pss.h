@@ -71,11 +71,10 @@
  *   PSS_PREPARE_BACKWARD  read by pss_forward only (the other calls ignore
  *     it; pss_prepare_backward does the same work as a call of its own): the
  *     forward also groups the batch's lookups by token for the backward.  For
- *     a batch with as many items as bags the grouping's first stage (every
- *     lookup's key and pooled row, and the first radix pass's digit counts)
- *     runs on `stream` ahead of the forward kernel, which then finds the
- *     batch's index and offset entries in the caches; the backward finishes
- *     the grouping on its stream.  Other forwards group the batch on a
+ *     small batches, and for batches with as many items as bags, only the
+ *     grouping's first stage is made (every lookup's key and pooled row), on
+ *     `stream`, by the forward kernel or a kernel ahead of it, and the
+ *     backward finishes it there.  Other batches are grouped on a
  *     library-owned stream that runs beside the forward kernel.  The next
  *     pss_backward_update on the same stream uses that grouping when its
  *     indices and offsets pointers, batch shape, hash parameters and options
@@ -171,6 +170,8 @@ enum {
  *           each token's sum is added once at its hashed addresses (float
  *           atomics; a token whose lookups span several of the 256-pair
  *           pieces of the grouped order adds one partial sum per piece).
+ *           Small batches are not sorted first: their pieces of 64 or 256
+ *           lookups are taken in the batch's own order.
  *   SPARSE  Alg. 1 sparse branch: the unique locations and summed values of
  *           pss_gradient_sparse, then the optimizer applied at those
  *           locations only.  No float atomics: bit-identical run to run.

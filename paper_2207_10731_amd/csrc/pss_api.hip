@@ -256,11 +256,12 @@ class CallScratch {
 // grouping waits for `start`, recorded after every earlier call on the
 // caller's stream (including the backward that read the buffer).
 //
-// For a batch with as many items as bags the call runs the grouping's first
-// stage (keygen) on the caller's stream ahead of the forward kernel instead
-// (`fused`).  Everything then happens on that stream (no side stream, no
-// events), and the backward finishes the grouping (the radix pass) before
-// its reduction.
+// For some batches the forward call makes the grouping's first stage (keygen)
+// on the caller's stream instead (`fused`: no side stream, no events): the
+// forward kernel itself for a small batch, whose backward takes the keygen as
+// it is (deposits_by_piece); a kernel ahead of it, with the first radix pass's
+// digit counts, for a large one with as many items as bags, whose backward
+// finishes the grouping.
 struct Prepared {
   std::mutex mu;
   hipStream_t side = nullptr;
@@ -269,7 +270,9 @@ struct Prepared {
   void* buf = nullptr;
   size_t bytes = 0;
   bool valid = false;  // a grouping waits for its backward
-  bool fused = false;  // valid: its keygen stage was run by the forward call
+  bool fused = false;    // valid: made by the forward call on the caller's stream
+  bool grouped = false;  // valid: `pairs` hold the whole grouping, else its keygen only
+  bool counted = false;  // valid, not grouped: with the first radix pass's digit counts
   const void* indices = nullptr;
   const void* offsets = nullptr;
   KParams made{};
@@ -293,7 +296,7 @@ bool capturing(hipStream_t stream) {
   return cs != hipStreamCaptureStatusNone;
 }
 
-int prepare_backward(const KParams& p, const void* indices, const void* offsets,
+int prepare_backward(const KParams& p, bool by_piece, const void* indices, const void* offsets,
                      hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return PSS_ERR_HIP;
@@ -342,9 +345,16 @@ int prepare_backward(const KParams& p, const void* indices, const void* offsets,
     }
     pr->bytes = need;
   }
-  if (pss::launch_group_sorted(p, indices, offsets, pr->buf, pr->side, &pr->pairs) != hipSuccess ||
-      hipEventRecord(pr->ready, pr->side) != hipSuccess)
-    return PSS_ERR_HIP;
+  hipError_t e;
+  if (by_piece) {
+    const pss::KeygenOut kg = pss::keygen_layout(p, pr->buf);
+    e = pss::launch_keygen(p, indices, offsets, kg.keys, kg.rows, kg.inv_len, pr->side);
+  } else {
+    e = pss::launch_group_sorted(p, indices, offsets, pr->buf, pr->side, &pr->pairs);
+  }
+  if (e != hipSuccess || hipEventRecord(pr->ready, pr->side) != hipSuccess) return PSS_ERR_HIP;
+  pr->grouped = !by_piece;
+  pr->counted = false;
   pr->indices = indices;
   pr->offsets = offsets;
   pr->made = p;
@@ -395,20 +405,33 @@ int prepare_fused(const KParams& p, const void* indices, const void* offsets, hi
   return PSS_OK;
 }
 
-void mark_fused(Prepared* pr) {
+void mark_fused(Prepared* pr, bool counted) {
   std::lock_guard<std::mutex> lock(pr->mu);
   pr->valid = true;
   pr->fused = true;
+  pr->grouped = false;
+  pr->counted = counted;
 }
 
-// The grouped pairs of a prepared grouping, on `stream`: wait for the
-// library stream's grouping, or finish the one whose keygen stage the
-// forward call ran.
-hipError_t prepared_pairs(Prepared* prep, const KParams& p, hipStream_t stream,
+// The pairs of a prepared grouping, on `stream` (after the library stream's
+// work): grouped by token (`group`: finished here if only the keygen was
+// made), or in any order.
+hipError_t prepared_pairs(Prepared* prep, const KParams& p, bool group, hipStream_t stream,
                           pss::GroupedPairs* pairs) {
-  if (prep->fused) return pss::finish_group_sorted(p, prep->buf, true, stream, pairs);
-  *pairs = prep->pairs;
-  return hipStreamWaitEvent(stream, prep->ready, 0);
+  if (!prep->fused) {
+    const hipError_t e = hipStreamWaitEvent(stream, prep->ready, 0);
+    if (e != hipSuccess) return e;
+  }
+  if (prep->grouped) {
+    *pairs = prep->pairs;
+    return hipSuccess;
+  }
+  if (group) return pss::finish_group_sorted(p, prep->buf, prep->counted, stream, pairs);
+  const pss::KeygenOut kg = pss::keygen_layout(p, prep->buf);
+  pairs->keys = kg.keys;
+  pairs->rows = kg.rows;
+  pairs->inv_len = kg.inv_len;
+  return hipSuccess;
 }
 
 // The grouping prepared by the last forward on `stream`, if it was made for
@@ -462,6 +485,7 @@ struct BackwardPlan {
   uint32_t variant = PSS_BWD_SORTED;  // ATOMIC, SORTED or SPARSE
   bool by_address = false;            // SORTED: records sorted by address tile
   bool runs = false;                  // ... the records being run sums (grouped by token)
+  bool by_piece = false;              // SORTED, not by address: one kernel, no grouping
   bool bf16 = false;
   bool fused = false;   // SGD on float32 storage: deposits go into `shared`
   size_t g_bytes = 0;   // float32 gradient buffer (unfused updates), 256-aligned
@@ -498,6 +522,7 @@ int plan_backward(void* shared, float* state, int64_t M, int32_t Z, int32_t d,
   plan->variant = variant;
   plan->by_address = variant == PSS_BWD_SORTED && (addr_asked || (auto_pick && by_address_auto(M, p)));
   plan->runs = plan->by_address && p.Z >= kRunsMinZ;
+  plan->by_piece = variant == PSS_BWD_SORTED && !plan->by_address && pss::deposits_by_piece(p);
   if (variant == PSS_BWD_SPARSE) {
     // Alg. 1 sparse branch: 256 bytes for the unique count, then its workspace
     plan->ws_bytes = 256 + pss::sparse_workspace_bytes(p);
@@ -540,7 +565,7 @@ hipError_t enqueue_backward(const BackwardPlan& plan, void* shared, float* state
     if (prep != nullptr) {
       // the grouping made ahead (on the library stream, or begun by the
       // forward call)
-      e = prepared_pairs(prep, p, stream, &pairs);
+      e = prepared_pairs(prep, p, true, stream, &pairs);
     } else {
       e = pss::launch_group_sorted(p, indices, offsets, group_ws, stream, &pairs);
     }
@@ -563,16 +588,21 @@ hipError_t enqueue_backward(const BackwardPlan& plan, void* shared, float* state
     return e;
   }
   if (!plan.fused) e = pss::launch_zero(dst, M, stream);
-  if (e == hipSuccess && prep != nullptr) {
-    // the grouping made ahead (on the library stream, or begun by the
-    // forward call)
-    pss::GroupedPairs pairs;
-    e = prepared_pairs(prep, p, stream, &pairs);
-    if (e == hipSuccess) e = pss::launch_reduce_sorted(dst, scale, p, pairs, grad_out, stream);
-  } else if (e == hipSuccess) {
-    e = plan.variant == PSS_BWD_SORTED
-            ? pss::launch_deposit_sorted(dst, scale, p, indices, offsets, grad_out, sort_ws, stream)
-            : pss::launch_deposit_atomic(dst, scale, p, indices, offsets, grad_out, stream);
+  pss::GroupedPairs pairs;
+  // the grouping made ahead (on the library stream, or begun by the forward
+  // call)
+  if (e == hipSuccess && prep != nullptr)
+    e = prepared_pairs(prep, p, !plan.by_piece, stream, &pairs);
+  if (e == hipSuccess) {
+    if (plan.by_piece)
+      e = pss::launch_deposit_pieces(dst, scale, p, indices, offsets,
+                                     prep != nullptr ? &pairs : nullptr, grad_out, stream);
+    else if (plan.variant == PSS_BWD_ATOMIC)
+      e = pss::launch_deposit_atomic(dst, scale, p, indices, offsets, grad_out, stream);
+    else if (prep != nullptr)
+      e = pss::launch_reduce_sorted(dst, scale, p, pairs, grad_out, stream);
+    else
+      e = pss::launch_deposit_sorted(dst, scale, p, indices, offsets, grad_out, sort_ws, stream);
   }
   if (e == hipSuccess && !plan.fused)
     e = pss::launch_optimizer(shared, plan.bf16, state, dst, M, lr, eps, stream);
@@ -652,24 +682,33 @@ int pss_forward(const void* shared, int64_t M, int32_t Z, int32_t d,
   const bool bf16 = hash_params->weight_dtype == PSS_BF16;
   pss::KeygenOut kg;
   Prepared* fused = nullptr;
+  bool ahead = false;
   if ((hash_params->flags & PSS_PREPARE_BACKWARD) && p.N > 0 && groups_by_token(M, p, hash_params) &&
       !capturing(stream)) {
-    // as many items as bags: the first stage runs ahead of the forward
-    // kernel, on `stream`; other batches are grouped on the library stream
-    if (pss::keygen_counts(p)) {
+    // small batches: the forward kernel writes the keygen; large ones with as
+    // many items as bags: a kernel ahead of it, with digit counts; others are
+    // grouped on the library stream beside it (26 x 32768 bags of 20 items: step
+    // 3128 us, with the keygen written by the forward kernel 3193 us)
+    const bool by_piece =
+        pss::deposits_by_piece(p) && !(hash_params->flags & PSS_DEPOSIT_BY_ADDRESS);
+    ahead = !by_piece && pss::keygen_counts(p);
+    if (by_piece || ahead) {
       if (prepare_fused(p, indices, offsets, stream, &kg, &fused) != PSS_OK) {
         (void)hipGetLastError();
         fused = nullptr;
+        kg = pss::KeygenOut{};
+        ahead = false;
       }
-    } else if (prepare_backward(p, indices, offsets, stream) != PSS_OK) {
+    } else if (prepare_backward(p, false, indices, offsets, stream) != PSS_OK) {
       (void)hipGetLastError();
     }
   }
   hipError_t e = hipSuccess;
-  if (fused != nullptr) e = pss::launch_keygen_counts(p, indices, offsets, kg, stream);
+  if (ahead) e = pss::launch_keygen_counts(p, indices, offsets, kg, stream);
   if (e == hipSuccess)
-    e = pss::launch_forward(shared, bf16, p, indices, offsets, out, stream, fused != nullptr);
-  if (e == hipSuccess && fused != nullptr) mark_fused(fused);
+    e = pss::launch_forward(shared, bf16, p, indices, offsets, out, stream, ahead,
+                            ahead ? pss::KeygenOut{} : kg);
+  if (e == hipSuccess && fused != nullptr) mark_fused(fused, ahead);
   return hip_status(e);
 }
 
@@ -681,7 +720,9 @@ int pss_prepare_backward(int64_t M, int32_t Z, int32_t d, const pss_hash_params*
   if (indices == nullptr && hash_params->num_indices > 0) return PSS_ERR_INVALID_ARG;
   const KParams p = make_params(M, Z, d, hash_params);
   if (p.N == 0 || !groups_by_token(M, p, hash_params) || capturing(stream)) return PSS_OK;
-  const int ps = prepare_backward(p, indices, offsets, stream);
+  const bool by_piece =
+      pss::deposits_by_piece(p) && !(hash_params->flags & PSS_DEPOSIT_BY_ADDRESS);
+  const int ps = prepare_backward(p, by_piece, indices, offsets, stream);
   if (ps != PSS_OK) (void)hipGetLastError();
   return ps;
 }
@@ -699,7 +740,8 @@ int pss_backward_update(void* shared, float* state, int64_t M, int32_t Z, int32_
                                  plan.variant == PSS_BWD_SORTED &&
                                      (!plan.by_address || plan.runs) && !capturing(stream),
                                  &prep_lock);
-  if (prep != nullptr) plan.ws_bytes = 0;  // the grouping is already made
+  // the grouping is already made, or needs no scratch
+  if (prep != nullptr || plan.by_piece) plan.ws_bytes = 0;
   CallScratch scratch;
   const size_t need = plan.g_bytes + plan.runs_bytes + plan.ws_bytes;
   if (need > 0) {

@@ -74,7 +74,7 @@ __device__ __forceinline__ void touch_batch(const KParams& p, const void* __rest
   auto touch = [&](const void* base, uint64_t n_entries) {
     const uint64_t a0 = reinterpret_cast<uint64_t>(base);
     const uint64_t c_lo = (a0 + 15) / 16, c_end = (a0 + n_entries * es) / 16;
-    constexpr int kPieces = 16;  // requested before any is used
+    constexpr int kPieces = 8;  // requested before any is used (16 take the kernels past 64 VGPRs)
     const uint64_t stride = static_cast<uint64_t>(touch_blocks) * kBlockThreads;
     for (uint64_t c0 = c_lo + static_cast<uint64_t>(blockIdx.x) * kBlockThreads + threadIdx.x;
          c0 < c_end; c0 += kPieces * stride) {
@@ -246,9 +246,9 @@ __device__ __forceinline__ void table_fence() {
 // items (d = 64, Z = 16, 64 MB array) 889 -> 811 us: the rate of random
 // 64-byte requests beyond the L2s.
 template <typename WT, int V, int LPB, bool SIGN>
-__global__ __launch_bounds__(kBlockThreads) void forward_bags_kernel(
+__global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out) {
+    const void* __restrict__ offsets, void* __restrict__ out, const KeygenOut kg) {
   constexpr int U = row_batch<V, LPB>();
   constexpr int GP = kWave / LPB;
   static_assert(U <= LPB, "one lane per item of the batch");
@@ -276,6 +276,10 @@ __global__ __launch_bounds__(kBlockThreads) void forward_bags_kernel(
   const uint32_t tC = t * p.C;
   uint32_t left = static_cast<uint32_t>(e1 - e);  // N < 2^32
   const uint32_t len = left;
+  // the lookups' keys and rows for the backward, when asked for
+  const bool keys = kg.keys != nullptr && blockIdx.y == 0;
+  const uint32_t row = b * p.T + t;
+  if (keys && p.mean && gl == 0 && len) kg.inv_len[row] = 1.f / static_cast<float>(len);
   typename Piece<V>::type acc = {};
   uint32_t ix = 0;
   if (gl < U && static_cast<uint32_t>(gl) < left)
@@ -285,6 +289,10 @@ __global__ __launch_bounds__(kBlockThreads) void forward_bags_kernel(
     const uint32_t h0 = item_hash(ix, tC, p.TC, p.a, p.b);
     if (gl < U && static_cast<uint32_t>(U + gl) < left)
       ix = index_at(indices, static_cast<uint64_t>(e + U + gl), p.idx32);
+    if (keys && static_cast<uint32_t>(gl) < n) {
+      kg.keys[e + gl] = h0;
+      kg.rows[e + gl] = row;
+    }
 #pragma unroll 1
     for (uint32_t k0 = 0; __ballot(k0 < n * rl.Cs); k0 += LPB) {
       const uint32_t k = k0 + gl;
@@ -339,9 +347,10 @@ __global__ __launch_bounds__(kBlockThreads) void forward_bags_kernel(
 // 26 x 65536 (5.1-5.4 TB/s); small batches are bound by the chain of
 // index load, hash, gather and store.
 template <typename WT, int V, int LPB, bool SIGN>
-__global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
+__global__ __launch_bounds__(kBlockThreads, 8) void forward_stream_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t touch_blocks) {
+    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t touch_blocks,
+    const KeygenOut kg) {
   constexpr int U = row_batch<V, LPB>();
   constexpr int GP = kWave / LPB;
   constexpr int NB = U * GP;
@@ -382,6 +391,8 @@ __global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
     ent[u] = tab[(i < nb ? i : 0u) * rl.Cs + jl];
     odd |= splits<V, SIGN>(ent[u], rl.kk, p.M);
   }
+  // the lookups' keys and rows for the backward, when asked for
+  const bool keys = kg.keys != nullptr && blockIdx.y == 0;
   if (__ballot(odd)) {
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
@@ -389,6 +400,7 @@ __global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
       const int64_t s0 = __shfl(o0, i), s1 = __shfl(o1, i);
       const uint32_t tCi = __shfl(tC, i);
       const uint64_t roi = __shfl(ro, i);
+      const uint32_t row = __shfl(b * p.T + t, i);
       if (static_cast<uint32_t>(i) >= nb) continue;
       const int64_t f0 = s0 < 0 ? 0 : (s0 > p.N ? p.N : s0);
       int64_t f1 = s1 < 0 ? 0 : (s1 > p.N ? p.N : s1);
@@ -398,9 +410,15 @@ __global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
       for (int64_t e = f0; e < f1; ++e) {
         const uint32_t h =
             item_hash(index_at(indices, static_cast<uint64_t>(e), p.idx32), tCi, p.TC, p.a, p.b);
+        if (keys && gl == 0) {
+          kg.keys[e] = h;
+          kg.rows[e] = row;
+        }
         const uint32_t en = item_entry<SIGN>(p, h, rl.jc);
         acc += sign_piece<SIGN>(gather_split<WT, V, SIGN>(w, en, rl.kk, p.M), en);
       }
+      if (keys && p.mean && gl == 0 && f1 > f0)
+        kg.inv_len[row] = 1.f / static_cast<float>(f1 - f0);
       if (p.mean && f1 > f0) acc /= static_cast<float>(f1 - f0);
       if (rl.act) store_piece(out, roi + rl.c, acc, p.rows_bf16);
     }
@@ -409,6 +427,12 @@ __global__ __launch_bounds__(kBlockThreads) void forward_stream_kernel(
   typename Piece<V>::type v[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) v[u] = gather<WT, V, SIGN>(w, ent[u], rl.kk, p.M);
+  if (keys && mine) {
+    const uint32_t row = b * p.T + t;
+    kg.keys[g] = h0;
+    kg.rows[g] = row;
+    if (p.mean) kg.inv_len[row] = 1.f;
+  }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int i = u * GP + grp;
@@ -623,30 +647,30 @@ static hipError_t launch_tiled(const WT* w, const KParams& p, const void* indice
 template <typename WT, int V, int LPB, bool SIGN>
 static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indices,
                                 const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch) {
+                               uint32_t touch, const KeygenOut& kg) {
   const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? row_batch<V, LPB>() : 1);
   const uint32_t blocks = grid_of((p.num_bags + per_wave - 1) / per_wave);
   if (blocks == 0) return hipErrorInvalidConfiguration;
   const dim3 grid(blocks, (p.d + LPB * V - 1) / (LPB * V));
   if (one_per_bag(p))
     hipLaunchKernelGGL((forward_stream_kernel<WT, V, LPB, SIGN>), grid, dim3(kBlockThreads), 0,
-                       stream, w, p, indices, offsets, out, touch);
+                       stream, w, p, indices, offsets, out, touch, kg);
   else
     hipLaunchKernelGGL((forward_bags_kernel<WT, V, LPB, SIGN>), grid, dim3(kBlockThreads), 0,
-                       stream, w, p, indices, offsets, out);
+                       stream, w, p, indices, offsets, out, kg);
   return hipGetLastError();
 }
 
 template <typename WT, int V, bool SIGN>
 static hipError_t launch_rows_v(const WT* w, const KParams& p, const void* indices,
                                 const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch) {
+                               uint32_t touch, const KeygenOut& kg) {
   const uint32_t lanes = (p.d + V - 1) / V;
-  if (lanes <= 4) return launch_rows_t<WT, V, 4, SIGN>(w, p, indices, offsets, out, stream, touch);
-  if (lanes <= 8) return launch_rows_t<WT, V, 8, SIGN>(w, p, indices, offsets, out, stream, touch);
-  if (lanes <= 16) return launch_rows_t<WT, V, 16, SIGN>(w, p, indices, offsets, out, stream, touch);
-  if (lanes <= 32) return launch_rows_t<WT, V, 32, SIGN>(w, p, indices, offsets, out, stream, touch);
-  return launch_rows_t<WT, V, 64, SIGN>(w, p, indices, offsets, out, stream, touch);
+  if (lanes <= 4) return launch_rows_t<WT, V, 4, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
+  if (lanes <= 8) return launch_rows_t<WT, V, 8, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
+  if (lanes <= 16) return launch_rows_t<WT, V, 16, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
+  if (lanes <= 32) return launch_rows_t<WT, V, 32, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
+  return launch_rows_t<WT, V, 64, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
 }
 
 // The tiled kernel is kept where gathering each distinct token of 64 bags
@@ -664,26 +688,30 @@ static bool tiled_applies(const KParams& p) {
 template <typename WT, bool SIGN>
 static hipError_t launch_fwd_s(const WT* w, const KParams& p, const void* indices,
                                const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch) {
-  if (tiled_applies<WT>(p)) return launch_tiled<WT, SIGN>(w, p, indices, offsets, out, stream, touch);
-  if (p.Z % 4 == 0) return launch_rows_v<WT, 4, SIGN>(w, p, indices, offsets, out, stream, touch);
-  return launch_rows_v<WT, 1, SIGN>(w, p, indices, offsets, out, stream, touch);
+                               uint32_t touch, const KeygenOut& kg) {
+  if (tiled_applies<WT>(p)) {
+    if (kg.keys != nullptr) return hipErrorInvalidValue;  // it does not write them
+    return launch_tiled<WT, SIGN>(w, p, indices, offsets, out, stream, touch);
+  }
+  if (p.Z % 4 == 0) return launch_rows_v<WT, 4, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
+  return launch_rows_v<WT, 1, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
 }
 
 template <typename WT>
 static hipError_t launch_fwd_w(const WT* w, const KParams& p, const void* indices,
                                const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch) {
-  if (p.sign_mode) return launch_fwd_s<WT, true>(w, p, indices, offsets, out, stream, touch);
-  return launch_fwd_s<WT, false>(w, p, indices, offsets, out, stream, touch);
+                               uint32_t touch, const KeygenOut& kg) {
+  if (p.sign_mode) return launch_fwd_s<WT, true>(w, p, indices, offsets, out, stream, touch, kg);
+  return launch_fwd_s<WT, false>(w, p, indices, offsets, out, stream, touch, kg);
 }
 
 hipError_t launch_forward(const void* w, bool bf16, const KParams& p, const void* indices,
-                          const void* offsets, void* out, hipStream_t stream, bool batch_read) {
+                          const void* offsets, void* out, hipStream_t stream, bool batch_read,
+                          const KeygenOut& kg) {
   const uint32_t touch = !batch_read && p.num_bags >= kTouchBags ? kTouchBlocks : 0u;
   if (bf16)
-    return launch_fwd_w(static_cast<const uint16_t*>(w), p, indices, offsets, out, stream, touch);
-  return launch_fwd_w(static_cast<const float*>(w), p, indices, offsets, out, stream, touch);
+    return launch_fwd_w(static_cast<const uint16_t*>(w), p, indices, offsets, out, stream, touch, kg);
+  return launch_fwd_w(static_cast<const float*>(w), p, indices, offsets, out, stream, touch, kg);
 }
 
 }  // namespace pss

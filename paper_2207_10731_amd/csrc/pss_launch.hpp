@@ -9,7 +9,8 @@
 namespace pss {
 
 // First stage of the grouping (keys, rows, the first radix pass's digit
-// counts, inv_len with mean pooling) as laid out in its workspace.
+// counts, inv_len with mean pooling) as laid out in its workspace
+// (keys == nullptr: none).
 struct KeygenOut {
   uint32_t* keys = nullptr;
   uint32_t* rows = nullptr;
@@ -20,9 +21,13 @@ struct KeygenOut {
 // Forward: pooled rows of every bag into out[B][T*d].
 // indices / offsets are int64 (int32 when p.idx32); out / grad rows are
 // float32 (bfloat16 when p.rows_bf16).  batch_read: the work just enqueued on
-// the stream has read indices and offsets (they are in the caches).
+// the stream has read indices and offsets (they are in the caches).  With
+// kg.keys the kernel also writes the lookups' keys, rows and inv_len there (no
+// digit counts; only where keygen_counts or deposits_by_piece sends it: the
+// tiled kernel, which meets neither, does not write them).
 hipError_t launch_forward(const void* w, bool bf16, const KParams& p, const void* indices,
-                          const void* offsets, void* out, hipStream_t stream, bool batch_read);
+                          const void* offsets, void* out, hipStream_t stream, bool batch_read,
+                          const KeygenOut& kg);
 
 // Atomic deposit: dst[addr] += scale * grad for every (item, dim).
 hipError_t launch_deposit_atomic(float* dst, float scale, const KParams& p, const void* indices,
@@ -59,6 +64,16 @@ hipError_t launch_group_sorted(const KParams& p, const void* indices, const void
 // Events recorded around every later reduce-and-deposit launch (both null:
 // none).
 void set_reduce_events(hipEvent_t before, hipEvent_t after);
+void reduce_events(hipEvent_t* before, hipEvent_t* after);  // both or neither
+
+// The sorted deposit of a small batch in one kernel, grouped within pieces of
+// consecutive lookups (deposits_by_piece: whether it is the faster form).
+// With pairs (the keygen of this batch: keys, rows and inv_len in item order)
+// indices and offsets are not read.
+bool deposits_by_piece(const KParams& p);
+hipError_t launch_deposit_pieces(float* dst, float scale, const KParams& p, const void* indices,
+                                 const void* offsets, const GroupedPairs* pairs, const void* grad,
+                                 hipStream_t stream);
 
 hipError_t launch_reduce_sorted(float* dst, float scale, const KParams& p, const GroupedPairs& g,
                                 const void* grad, hipStream_t stream);

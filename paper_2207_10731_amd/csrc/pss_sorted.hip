@@ -859,6 +859,11 @@ void set_reduce_events(hipEvent_t before, hipEvent_t after) {
   g_reduce_before.store(before);
   g_reduce_after.store(after);
 }
+void reduce_events(hipEvent_t* before, hipEvent_t* after) {
+  *before = g_reduce_before.load();
+  *after = g_reduce_after.load();
+  if (*before == nullptr || *after == nullptr) *before = *after = nullptr;
+}
 
 template <int EPL, int U, bool SIGN, typename GT, bool REC>
 static hipError_t launch_reduce_t(float* dst, float scale, const KParams& p, const uint32_t* keys,
