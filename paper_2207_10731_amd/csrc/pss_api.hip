@@ -553,6 +553,9 @@ hipError_t enqueue_backward(const BackwardPlan& plan, void* shared, float* state
   const KParams& p = plan.p;
   if (plan.variant == PSS_BWD_SPARSE) {
     // the optimizer is applied at each unique location as it is summed
+    if (pss::sparse_by_tile(p, false))
+      return pss::launch_update_tiles(p, indices, offsets, grad_out, ws, shared, plan.bf16, state,
+                                      lr, eps, stream);
     uint32_t* count = static_cast<uint32_t*>(ws);
     return pss::launch_sparse_update(p, indices, offsets, grad_out, static_cast<char*>(ws) + 256,
                                      count, shared, plan.bf16, state, lr, eps, stream);
@@ -785,20 +788,25 @@ int pss_gradient_sparse(int64_t M, int32_t Z, int32_t d, const pss_hash_params* 
   if (p.N * static_cast<int64_t>(p.C) >= (1ll << 31)) return PSS_ERR_UNSUPPORTED;
   if (capacity < sparse_capacity(M, p)) return PSS_ERR_INVALID_ARG;
   if (p.N > 0 && (locations == nullptr || values == nullptr)) return PSS_ERR_INVALID_ARG;
-  const size_t ws_bytes = 256 + (p.N > 0 ? pss::sparse_workspace_bytes(p) : 0);
+  const bool by_tile = p.N > 0 && pss::sparse_by_tile(p, true);
+  const size_t ws_bytes = by_tile ? pss::tile_workspace_bytes(p, true)
+                                  : 256 + (p.N > 0 ? pss::sparse_workspace_bytes(p) : 0);
   CallScratch scratch;
   st = scratch.take(ws_bytes, stream);
   if (st != PSS_OK) return st;
   void* ws = scratch.ptr();
   uint32_t* count = static_cast<uint32_t*>(ws);
   hipError_t e = hipSuccess;
-  if (p.N == 0) {
+  if (by_tile) {
+    e = pss::launch_gradient_tiles(p, indices, offsets, grad_out, ws, locations, values, capacity,
+                                   num_unique, stream);
+  } else if (p.N == 0) {
     e = pss::launch_zero(reinterpret_cast<float*>(count), 1, stream);
   } else {
     e = pss::launch_gradient_sparse(p, indices, offsets, grad_out, static_cast<char*>(ws) + 256,
                                     locations, values, capacity, count, stream);
   }
-  if (e == hipSuccess) e = pss::launch_store_count(count, num_unique, stream);
+  if (e == hipSuccess && !by_tile) e = pss::launch_store_count(count, num_unique, stream);
   const hipError_t ef = scratch.done();
   return (e != hipSuccess || ef != hipSuccess) ? PSS_ERR_HIP : PSS_OK;
 }

@@ -78,6 +78,27 @@ hipError_t launch_deposit_pieces(float* dst, float scale, const KParams& p, cons
 hipError_t launch_reduce_sorted(float* dst, float scale, const KParams& p, const GroupedPairs& g,
                                 const void* grad, hipStream_t stream);
 
+// The same pieces' run sums as records instead: rows of `sums` (N x d floats)
+// and N * C (base, row * C + j) records, base 0xffffffff where there is none.
+// Requires p.N * p.C < 2^32.
+hipError_t launch_piece_records(float* sums, const KParams& p, const void* indices,
+                                const void* offsets, const void* grad, uint32_t* rec_keys,
+                                uint32_t* rec_ids, hipStream_t stream);
+
+// Sparse gradient and update of a small batch by array tile (sparse_by_tile:
+// whether it applies); the same results as launch_gradient_sparse and
+// launch_sparse_update.  workspace: tile_workspace_bytes(p) bytes (not more
+// than sparse_workspace_bytes for the update).
+bool sparse_by_tile(const KParams& p, bool list);
+size_t tile_workspace_bytes(const KParams& p, bool list);
+hipError_t launch_gradient_tiles(const KParams& p, const void* indices, const void* offsets,
+                                 const void* grad, void* workspace, uint32_t* locations,
+                                 float* values, int64_t capacity, int64_t* num_unique,
+                                 hipStream_t stream);
+hipError_t launch_update_tiles(const KParams& p, const void* indices, const void* offsets,
+                               const void* grad, void* workspace, void* w, bool bf16, float* state,
+                               float lr, float eps, hipStream_t stream);
+
 // Building blocks of the sorted path, shared with the sparse-gradient path.
 // keygen: keys[e] = item part of the hash of lookup e, rows[e] = b*T + t;
 // with mean pooling also inv_len[b*T + t] = 1 / |bag| (nonempty bags).
@@ -89,7 +110,10 @@ hipError_t launch_keygen(const KParams& p, const void* indices, const void* offs
 // pairs is min(n, *n_dev) (read on the device; n sizes the launch).  With
 // first_counted the first pass's per-tile digit counts are already at the
 // start of scratch (written while the keys were made).
+// After a single pass the digit totals (256 words) stand in scratch at
+// radix_totals(scratch, n).
 size_t radix_scratch_bytes(int64_t n);
+const uint32_t* radix_totals(const uint32_t* scratch, int64_t n);
 hipError_t radix_sort_pairs(uint32_t*& keys, uint32_t*& vals, uint32_t* ktmp, uint32_t* vtmp,
                             int64_t n, int bits, uint32_t* scratch, hipStream_t stream,
                             const uint32_t* n_dev = nullptr, bool first_counted = false,

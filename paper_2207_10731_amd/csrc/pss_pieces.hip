@@ -43,12 +43,18 @@ __device__ __forceinline__ uint64_t bag_search(const void* __restrict__ offsets,
   return lo;
 }
 
-template <int EPL, int LPB, int P, bool SIGN, bool I32, typename GT>
+// With REC nothing is deposited: the run that begins at merged position q
+// becomes row p0 + q of dst (N x d floats, its sign factors applied), and every
+// position and chunk j a record (rec_keys, rec_ids): the chunk's base and
+// (p0 + q) * C + j, or kNoChunk where no run begins or the chunk is not read.
+// Every sum is then taken in a fixed order.
+constexpr uint32_t kNoChunk = 0xffffffffu;
+template <int EPL, int LPB, int P, bool SIGN, bool I32, bool REC, typename GT>
 __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
     float* __restrict__ dst, const float scale, const KParams p, const void* __restrict__ indices,
     const void* __restrict__ offsets, const uint32_t* __restrict__ keys,
     const uint32_t* __restrict__ rows, const float* __restrict__ inv_len,
-    const GT* __restrict__ grad) {
+    const GT* __restrict__ grad, uint32_t* __restrict__ rec_keys, uint32_t* __restrict__ rec_ids) {
   constexpr int GP = kWave / LPB;           // lane groups of a wavefront
   constexpr int NG = 4 * P / kWave * GP;    // ... of the workgroup
   constexpr int S = P / NG;                 // pairs per group
@@ -207,7 +213,23 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
   request(0);
   // chunk entries of every pair, while the rows are on their way
   const bool use_tab = p.C <= static_cast<uint32_t>(kTabChunks);
-  if (use_tab) {
+  if (REC && blockIdx.y == 0) {
+    for (uint32_t k = tid; k < static_cast<uint32_t>(cnt) * p.C; k += 4 * P) {
+      const uint32_t i = k / p.C, j = k - i * p.C;
+      const uint32_t h = mk[i];
+      uint32_t base = kNoChunk;
+      if (i == 0 || mk[i - 1] != h) {
+        const uint32_t ent = chunk_entry<SIGN>(
+            fast_mod(add_mod_p(h, chunk_step(p.a, j)), p.fm_c, p.M),
+            SIGN ? add_mod_p(sign_hash0(h, p.s_alpha, p.s_beta), chunk_step(p.a2, j)) : 0u, p);
+        if (!SIGN || ent != kSkip) base = ent & 0x7fffffffu;
+      }
+      const uint64_t at = static_cast<uint64_t>(p0) * p.C + k;
+      rec_keys[at] = base;
+      rec_ids[at] = static_cast<uint32_t>(at);
+    }
+  }
+  if (use_tab && (!REC || SIGN)) {
     for (uint32_t k = tid; k < static_cast<uint32_t>(cnt) * p.C; k += 4 * P) {
       const uint32_t i = k / p.C, j = k - i * p.C;
       const uint32_t h = mk[i];
@@ -225,6 +247,13 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
   }
   __syncthreads();
   auto deposit = [&](const float* acc, int q) {
+    if (REC && !SIGN) {
+      float* row = dst + (static_cast<uint64_t>(p0) + q) * p.d;
+#pragma unroll
+      for (int r = 0; r < EPL; ++r)
+        if (act[r]) row[cc[r]] = acc[r];
+      return;
+    }
     const uint32_t h = use_tab ? 0u : mk[q];
     const uint32_t h2 = SIGN && !use_tab ? sign_hash0(h, p.s_alpha, p.s_beta) : 0u;
 #pragma unroll
@@ -236,6 +265,10 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
                                       add_mod_p(h2, SIGN ? chunk_step(p.a2, jj[r]) : 0u), p);
       const Elem el = elem_of<SIGN>(ent, kk[r], p.M);
       const float x = scale * acc[r];
+      if (REC) {
+        dst[(static_cast<uint64_t>(p0) + q) * p.d + cc[r]] = apply_sign(x, el);
+        continue;
+      }
       if (!SIGN || el.read) unsafeAtomicAdd(dst + el.m, SIGN ? apply_sign(x, el) : x);
     }
   };
@@ -245,6 +278,7 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
   // the group's first run began in an earlier group's pairs
   bool head = q0 > 0 && nq > 0 && mk[q0] == mk[q0 - 1];
   bool tail = false;  // its last run goes on in the next group's pairs
+  int start = q0;     // where its current run begins
 #pragma unroll 1
   for (int u0 = 0; u0 < S; u0 += U) {
     if (u0 > 0) request(u0);
@@ -263,8 +297,9 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
             for (int r = 0; r < EPL; ++r) headv[grp][LPB * r + gl] = acc[r];
             head = false;
           } else {
-            deposit(acc, q);
+            deposit(acc, start);
           }
+          start = q + 1;
 #pragma unroll
           for (int r = 0; r < EPL; ++r) acc[r] = 0.f;
         }
@@ -284,29 +319,35 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
       for (int r = 0; r < EPL; ++r) acc[r] += headv[k][LPB * r + gl];
       if (!through[k]) break;
     }
-    deposit(acc, q0 + nq - 1);
+    deposit(acc, start);
   }
 }
 
-template <int EPL, int LPB, int P, bool SIGN, typename GT>
+// What a launch writes besides dst: nothing, or records.
+struct PieceRecords {
+  uint32_t* keys = nullptr;
+  uint32_t* ids = nullptr;
+};
+
+template <int EPL, int LPB, int P, bool SIGN, bool REC, typename GT>
 static hipError_t launch_pieces_t(float* dst, float scale, const KParams& p, const void* indices,
                                   const void* offsets, const GroupedPairs* pairs, const GT* grad,
-                                  hipStream_t stream) {
+                                  const PieceRecords& rec, hipStream_t stream) {
   const dim3 grid(static_cast<uint32_t>((p.N + P - 1) / P), (p.d + LPB * EPL - 1) / (LPB * EPL));
   const uint32_t* keys = pairs != nullptr ? pairs->keys : nullptr;
   const uint32_t* rows = pairs != nullptr ? pairs->rows : nullptr;
   const float* il = pairs != nullptr ? pairs->inv_len : nullptr;
   const dim3 block(4 * P);
-  hipEvent_t before, after;
-  reduce_events(&before, &after);
-  const auto kernel = p.idx32 ? deposit_pieces_kernel<EPL, LPB, P, SIGN, true, GT>
-                              : deposit_pieces_kernel<EPL, LPB, P, SIGN, false, GT>;
+  hipEvent_t before = nullptr, after = nullptr;
+  if (!REC) reduce_events(&before, &after);
+  const auto kernel = p.idx32 ? deposit_pieces_kernel<EPL, LPB, P, SIGN, true, REC, GT>
+                              : deposit_pieces_kernel<EPL, LPB, P, SIGN, false, REC, GT>;
   if (before != nullptr)  // the timing hook: the dispatch records both events
     hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, before, after, 0u, dst, scale, p, indices,
-                          offsets, keys, rows, il, grad);
+                          offsets, keys, rows, il, grad, rec.keys, rec.ids);
   else
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, dst, scale, p, indices, offsets, keys, rows,
-                       il, grad);
+                       il, grad, rec.keys, rec.ids);
   return hipGetLastError();
 }
 
@@ -315,43 +356,48 @@ static hipError_t launch_pieces_t(float* dst, float scale, const KParams& p, con
 // shorter pieces make more deposits).
 constexpr int64_t kSmallPieceItems = 1 << 15;
 
-template <int EPL, int LPB, bool SIGN, typename GT>
-static hipError_t launch_pieces_p(float* dst, float scale, const KParams& p, const void* indices,
-                                  const void* offsets, const GroupedPairs* pairs, const GT* grad,
-                                  hipStream_t stream) {
-  if (p.N <= kSmallPieceItems)
-    return launch_pieces_t<EPL, LPB, 64, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
-  return launch_pieces_t<EPL, LPB, 256, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
+template <int EPL, int LPB, bool SIGN, bool REC, typename GT, typename... A>
+static hipError_t launch_pieces_p(float* dst, float scale, const KParams& p, A... a) {
+  if (p.N <= kSmallPieceItems) return launch_pieces_t<EPL, LPB, 64, SIGN, REC, GT>(dst, scale, p, a...);
+  return launch_pieces_t<EPL, LPB, 256, SIGN, REC, GT>(dst, scale, p, a...);
 }
 
-template <bool SIGN, typename GT>
-static hipError_t launch_pieces_s(float* dst, float scale, const KParams& p, const void* indices,
-                                  const void* offsets, const GroupedPairs* pairs, const GT* grad,
-                                  hipStream_t stream) {
-  if (p.d <= 16) return launch_pieces_p<1, 16, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
-  if (p.d <= 32) return launch_pieces_p<1, 32, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
-  if (p.d <= 64) return launch_pieces_p<1, 64, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
-  if (p.d <= 128) return launch_pieces_p<2, 64, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
-  return launch_pieces_p<4, 64, SIGN>(dst, scale, p, indices, offsets, pairs, grad, stream);
+template <bool SIGN, bool REC, typename GT, typename... A>
+static hipError_t launch_pieces_s(float* dst, float scale, const KParams& p, A... a) {
+  if (p.d <= 16) return launch_pieces_p<1, 16, SIGN, REC, GT>(dst, scale, p, a...);
+  if (p.d <= 32) return launch_pieces_p<1, 32, SIGN, REC, GT>(dst, scale, p, a...);
+  if (p.d <= 64) return launch_pieces_p<1, 64, SIGN, REC, GT>(dst, scale, p, a...);
+  if (p.d <= 128) return launch_pieces_p<2, 64, SIGN, REC, GT>(dst, scale, p, a...);
+  return launch_pieces_p<4, 64, SIGN, REC, GT>(dst, scale, p, a...);
 }
 
-template <typename GT>
+template <bool REC, typename GT>
 static hipError_t launch_pieces_g(float* dst, float scale, const KParams& p, const void* indices,
-                                  const void* offsets, const GroupedPairs* pairs, const GT* grad,
-                                  hipStream_t stream) {
-  if (p.sign_mode) return launch_pieces_s<true>(dst, scale, p, indices, offsets, pairs, grad, stream);
-  return launch_pieces_s<false>(dst, scale, p, indices, offsets, pairs, grad, stream);
+                                  const void* offsets, const GroupedPairs* pairs, const void* grad,
+                                  const PieceRecords& rec, hipStream_t stream) {
+  const GT* g = static_cast<const GT*>(grad);
+  if (p.sign_mode)
+    return launch_pieces_s<true, REC, GT>(dst, scale, p, indices, offsets, pairs, g, rec, stream);
+  return launch_pieces_s<false, REC, GT>(dst, scale, p, indices, offsets, pairs, g, rec, stream);
 }
 
 hipError_t launch_deposit_pieces(float* dst, float scale, const KParams& p, const void* indices,
                                  const void* offsets, const GroupedPairs* pairs, const void* grad,
                                  hipStream_t stream) {
   if (p.N == 0) return hipSuccess;
+  const PieceRecords none;
   if (p.rows_bf16)
-    return launch_pieces_g(dst, scale, p, indices, offsets, pairs,
-                           static_cast<const uint16_t*>(grad), stream);
-  return launch_pieces_g(dst, scale, p, indices, offsets, pairs, static_cast<const float*>(grad),
-                         stream);
+    return launch_pieces_g<false, uint16_t>(dst, scale, p, indices, offsets, pairs, grad, none, stream);
+  return launch_pieces_g<false, float>(dst, scale, p, indices, offsets, pairs, grad, none, stream);
+}
+
+hipError_t launch_piece_records(float* sums, const KParams& p, const void* indices,
+                                const void* offsets, const void* grad, uint32_t* rec_keys,
+                                uint32_t* rec_ids, hipStream_t stream) {
+  const PieceRecords rec{rec_keys, rec_ids};
+  if (p.rows_bf16)
+    return launch_pieces_g<true, uint16_t>(sums, 1.f, p, indices, offsets, nullptr, grad, rec, stream);
+  return launch_pieces_g<true, float>(sums, 1.f, p, indices, offsets, nullptr, grad, rec, stream);
 }
 
 // Where one kernel is the faster form.  It saves three or four launches (25

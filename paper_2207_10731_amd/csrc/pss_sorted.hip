@@ -783,6 +783,10 @@ size_t radix_scratch_bytes(int64_t n) {
   return (nblocks * kBins + kBins + static_cast<uint64_t>(kBins) * scan_chunks(static_cast<uint32_t>(nblocks))) * 4 + 256;
 }
 
+const uint32_t* radix_totals(const uint32_t* scratch, int64_t n) {
+  return scratch + (static_cast<uint64_t>(n) + kSortTile - 1) / kSortTile * kBins;
+}
+
 size_t sorted_workspace_bytes(const KParams& p) {
   size_t s = static_cast<size_t>(p.N) * 16 + radix_scratch_bytes(p.N);
   if (p.mean) s += (p.num_bags * 4 + 255) & ~uint64_t(255);

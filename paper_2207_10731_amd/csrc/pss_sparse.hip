@@ -2,7 +2,7 @@
 // unique locations that any lookup reads and the summed output gradient at
 // each of them.  Cost follows the number of distinct tokens in the batch,
 // not M.  Every sum is taken in a fixed order, so the result is bit-identical
-// from run to run.
+// from run to run.  (Small batches: pss_tiles.hip.)
 //
 //   group      keygen + radix sort on the item hash (as the sorted deposit);
 //              piece_runs sorts each 64-pair piece by the full hash in

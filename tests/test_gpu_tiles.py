@@ -1,0 +1,76 @@
+"""GPU parity of the small batches' sparse gradient and update by array tile (Alg. 1,
+sparse branch) against the oracle: lane groups of 8 to 64 lanes, arrays below and of two tiles (of
+4096 elements), of a ragged last tile shorter than a chunk, of several and of
+hundreds of tiles (super tiles of one and of more tiles), chunks wrapping past
+the end, many records of one chunk, and the sizes just past the rule's limits
+(the general pipeline).  Two runs give the same bits.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+import parity
+from oracle import pss_oracle as o
+from paper_2207_10731_amd import pss
+from parity import Layer
+
+pytestmark = pytest.mark.gpu
+
+C2 = synth.get("c2")
+
+
+def _list(L, g):
+    wl = L.wl
+    cap = min(wl.M, L.x.N * wl.d)
+    loc = torch.zeros(cap, dtype=torch.int32, device=L.dev)
+    val = torch.zeros(cap, dtype=torch.float32, device=L.dev)
+    n = torch.zeros(1, dtype=torch.int64, device=L.dev)
+    gd = torch.from_numpy(g).to(L.dev)
+    pss.pss_gradient_sparse(wl.M, wl.Z, wl.d, L.hp, L.indices, L.offsets,
+                            gd.to(torch.bfloat16) if L.rows_bf16 else gd, loc, val, n)
+    u = int(n.item())
+    return loc[:u].cpu().numpy().view(np.uint32), val[:u].cpu().numpy()
+
+
+def _check(wl, **kw):
+    L = Layer(wl, flags=pss.PSS_BWD_SPARSE, s0=0.1, **kw)
+    g = synth.make_grad(L.wl, B=L.B)
+    loc, val = _list(L, g)
+    again = _list(L, g)
+    assert np.array_equal(loc, again[0]) and np.array_equal(val.view(np.uint32), again[1].view(np.uint32))
+    w_ref, s_ref, G, A, _ = L.ref_backward(g)
+    # every element that a chunk reads, whatever its sum (an element whose
+    # gradients are all exactly 0 does not occur in N(0, 1) draws)
+    assert np.array_equal(loc, np.flatnonzero(A > 0).astype(np.uint32))
+    assert np.all(np.abs(val - G[loc]) <= 1e-5 * A[loc])
+    L.backward(g)
+    s_gpu = None if L.state is None else L.state.cpu().numpy()
+    parity.check_update(L, L.weights(), s_gpu, w_ref, s_ref, G, A, L.wl.lr)
+
+
+@pytest.mark.parametrize("M", [1100, 4100, 8191, 8192, 8193, 12288 + 13, 30_000, 255 * 4096,
+                               255 * 4096 + 1, 3_000_001])
+@pytest.mark.parametrize("d,Z", [(16, 4), (24, 8), (48, 16), (60, 20), (64, 32), (66, 33),
+                                 (128, 128), (1024, 1024)])
+def test_tiles(d, Z, M):
+    B = 60 if d <= 128 else 9
+    for kw in (dict(), dict(sign="sparse", mean=True, idx32=True, rows_bf16=True)):
+        wl = C2.scaled(T=3, B=B, d=d, Z=Z, M=M, cardinality="fixed:40", optimizer="adagrad",
+                       bag="one" if not kw else "poisson:4:0:20",
+                       weight_dtype="bf16" if kw else "f32")
+        print(f"tiles d={d} Z={Z} M={M} {kw}", flush=True)
+        _check(wl, **kw)
+
+
+@pytest.mark.parametrize("T,B,M", [
+    (2, 16384, 40_000),    # 3 tokens per table: hundreds of records of one chunk
+    (1, 1 << 18, 5_000_000),      # the largest batch
+    (1, (1 << 18) + 1, 5_000_000),
+    (4, 4096, 4096 * 4096),       # the most tiles of a list
+    (4, 4096, 4096 * 4096 + 1),
+])
+def test_tile_limits(T, B, M):
+    wl = C2.scaled(T=T, B=B, d=16, Z=16, M=M, cardinality="fixed:3" if M < 100_000 else "fixed:9000")
+    print(f"tile limits T={T} B={B} M={M}", flush=True)
+    _check(wl)
