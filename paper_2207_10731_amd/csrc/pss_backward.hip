@@ -167,17 +167,61 @@ hipError_t launch_deposit_atomic(float* dst, float scale, const KParams& p, cons
 // weights this pass has just written, which the next forward gathers,
 // rather than the state streamed beside them (bfloat16 row-hash workload,
 // 128 MB array and 256 MB state: that forward 876 -> 754 us).
+//
+// A lane takes 4 consecutive elements (16-byte pieces, 8 of bfloat16; the
+// arrays may be aligned to one element only) and reads weights and state of
+// a piece only when one of its sums is not 0; the others of the piece are written
+// back as they are.  One element per lane before, per call: 64 M elements (bfloat16,
+// Adagrad) 227 -> 160 us (6.4 TB/s), 16 M (float32, Adagrad) 57 -> 48 us, half of
+// them touched 32 -> 19 us, 1.3 M 8.0 -> 6.0 us.
+typedef float opt_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t opt_h4 __attribute__((ext_vector_type(4), aligned(2)));
+
 template <typename WT, bool ADAGRAD>
 __global__ __launch_bounds__(kBlockThreads) void optimizer_kernel(
     WT* __restrict__ w, float* __restrict__ s, const float* __restrict__ G, const int64_t M,
     const float lr, const float eps) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlockThreads;
-  for (int64_t m = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x; m < M;
-       m += stride) {
-    const float g = __builtin_nontemporal_load(G + m);
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x;
+  const int64_t pieces = M / 4;
+  for (int64_t q = first; q < pieces; q += stride) {
+    const int64_t m = q * 4;
+    const opt_f4 g = __builtin_nontemporal_load(reinterpret_cast<const opt_f4*>(G + m));
+    if (g.x == 0.f && g.y == 0.f && g.z == 0.f && g.w == 0.f) continue;
+    opt_f4 so = {0.f, 0.f, 0.f, 0.f};
+    if (ADAGRAD) so = __builtin_nontemporal_load(reinterpret_cast<const opt_f4*>(s + m));
+    opt_f4 upd;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (ADAGRAD) {
+        if (g[i] != 0.f) so[i] = so[i] + g[i] * g[i];
+        upd[i] = lr * g[i] / (sqrtf(so[i]) + eps);
+      } else {
+        upd[i] = lr * g[i];
+      }
+    }
+    if constexpr (sizeof(WT) == 4) {
+      opt_f4* wp = reinterpret_cast<opt_f4*>(w + m);
+      opt_f4 x = *wp;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (g[i] != 0.f) x[i] = x[i] - upd[i];
+      *wp = x;
+    } else {
+      opt_h4* wp = reinterpret_cast<opt_h4*>(w + m);
+      opt_h4 x = *wp;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (g[i] != 0.f) x[i] = f32_to_bf16_rne(bf16_to_f32(x[i]) - upd[i]);
+      *wp = x;
+    }
+    if (ADAGRAD) __builtin_nontemporal_store(so, reinterpret_cast<opt_f4*>(s + m));
+  }
+  const int64_t m = pieces * 4 + first;  // the last M % 4
+  if (m < M) {
+    const float g = G[m];
     if (g != 0.f)
-      update_loaded<WT, ADAGRAD, true>(w, s, m, g, load_weight64(w, m),
-                                       ADAGRAD ? __builtin_nontemporal_load(s + m) : 0.f, lr, eps);
+      update_loaded<WT, ADAGRAD, true>(w, s, m, g, load_weight64(w, m), ADAGRAD ? s[m] : 0.f, lr, eps);
   }
 }
 
@@ -214,6 +258,7 @@ hipError_t launch_optimizer(void* w, bool bf16, float* state, const float* G, in
 __global__ __launch_bounds__(kBlockThreads) void zero_kernel(float* __restrict__ dst,
                                                              const int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlockThreads;
+  // 4-byte lanes: 16-byte ones fill 256 MB in 45 us against 34
   for (int64_t m = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x; m < n;
        m += stride)
     dst[m] = 0.f;
