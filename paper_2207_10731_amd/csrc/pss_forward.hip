@@ -57,25 +57,42 @@ __device__ __forceinline__ int64_t offset_at(const void* off, uint64_t g, uint32
              : static_cast<const int64_t*>(off)[g];
 }
 
-// The first `touch_blocks` workgroups read the batch's index and offset
-// arrays once, in whole 16-byte pieces lying inside them, before their own
-// work.  After a backward the arrays lie in HBM, where the index loads of
-// the later wavefronts would queue behind the write stream; read up front at
-// the streaming rate they are found in the memory-side cache (26 x 65536
-// rows in a training step: 252 -> 176 us; 26 x 16384: 58.8 -> 46.6 us).
-constexpr uint32_t kTouchBlocks = 256;      // one workgroup per compute unit
-constexpr uint64_t kTouchBags = 1ull << 18;  // smaller batches run in one generation of workgroups
-__device__ __forceinline__ void touch_batch(const KParams& p, const void* __restrict__ indices,
+// What the first kTouchBlocks workgroups (one per compute unit) read once before their
+// own work, in whole 16-byte pieces lying inside it, at the streaming rate:
+// later reads then find it in the memory-side cache.
+//  index  the batch's index and offset arrays.  After a backward they lie
+//         in HBM, where the index loads of the later wavefronts would queue
+//         behind the write stream (26 x 65536 rows in a training step:
+//         252 -> 176 us; 26 x 16384: 58.8 -> 46.6 us).  For batches of several
+//         generations of workgroups.
+//  bytes  the shared array, when it is larger than the L2s but fits the
+//         memory-side cache beside other data and the batch gathers 8 times its size or
+//         more.  Where other work has evicted it since its last use, each
+//         of its lines would otherwise be fetched by a random read (128 MB
+//         array, 26 x 262144 rows of 256 bytes: 970 -> 751 us, the training step
+//         2156 -> 1932 us).  Where it has not (the same step over and over, nothing
+//         else running), the pass costs 17 to 28 us of 1860.
+struct Touch {
+  uint32_t index = 0;
+  uint64_t bytes = 0;
+};
+constexpr uint32_t kTouchBlocks = 256;
+constexpr uint64_t kTouchBags = 1ull << 18;
+constexpr uint64_t kTouchMaxBytes = 192ull << 20;  // of the 256 MiB memory-side cache
+__device__ __forceinline__ void touch_batch(const KParams& p, const void* __restrict__ w,
+                                            const void* __restrict__ indices,
                                             const void* __restrict__ offsets,
-                                            void* __restrict__ out, const uint32_t touch_blocks) {
-  if (blockIdx.x >= touch_blocks || blockIdx.y != 0) return;
+                                            void* __restrict__ out, const Touch& touch) {
+  if (blockIdx.x >= kTouchBlocks || blockIdx.y != 0) return;
+  if (!touch.index && !touch.bytes) return;
   const uint64_t es = p.idx32 ? 4 : 8;
   uint32_t seen = 0;
-  auto touch = [&](const void* base, uint64_t n_entries) {
+  auto read = [&](const void* base, uint64_t bytes) {
     const uint64_t a0 = reinterpret_cast<uint64_t>(base);
-    const uint64_t c_lo = (a0 + 15) / 16, c_end = (a0 + n_entries * es) / 16;
+    const uint64_t c_lo = (a0 + 15) / 16, c_end = (a0 + bytes) / 16;
     constexpr int kPieces = 8;  // requested before any is used (16 take the kernels past 64 VGPRs)
-    const uint64_t stride = static_cast<uint64_t>(touch_blocks) * kBlockThreads;
+    const uint64_t blocks = gridDim.x < kTouchBlocks ? gridDim.x : kTouchBlocks;
+    const uint64_t stride = blocks * kBlockThreads;
     for (uint64_t c0 = c_lo + static_cast<uint64_t>(blockIdx.x) * kBlockThreads + threadIdx.x;
          c0 < c_end; c0 += kPieces * stride) {
       uint4 v4[kPieces];
@@ -88,8 +105,11 @@ __device__ __forceinline__ void touch_batch(const KParams& p, const void* __rest
       for (int k = 0; k < kPieces; ++k) seen ^= v4[k].x ^ v4[k].y ^ v4[k].z ^ v4[k].w;
     }
   };
-  touch(indices, static_cast<uint64_t>(p.N));
-  touch(offsets, p.num_bags + 1);
+  if (touch.index) {
+    read(indices, static_cast<uint64_t>(p.N) * es);
+    read(offsets, (p.num_bags + 1) * es);
+  }
+  if (touch.bytes) read(w, touch.bytes);
   // never true (N >= 0): keeps the loads
   if (seen == 0x9e3779b9u && p.N < 0) static_cast<uint32_t*>(out)[threadIdx.x] = seen;
 }
@@ -349,13 +369,13 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
 template <typename WT, int V, int LPB, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads, 8) void forward_stream_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t touch_blocks,
+    const void* __restrict__ offsets, void* __restrict__ out, const Touch touch,
     const KeygenOut kg) {
   constexpr int U = row_batch<V, LPB>();
   constexpr int GP = kWave / LPB;
   constexpr int NB = U * GP;
   static_assert(NB <= kWave, "one lane per bag");
-  touch_batch(p, indices, offsets, out, touch_blocks);
+  touch_batch(p, w, indices, offsets, out, touch);
   __shared__ uint32_t tab_all[kWavesPerBlock][NB * LPB];
   const int lane = threadIdx.x & (kWave - 1);
   const int grp = lane / LPB, gl = lane % LPB;
@@ -510,8 +530,8 @@ __device__ __forceinline__ void forward_onehot_tile(
 template <typename WT, int EPL, int U, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const uint32_t touch_blocks) {
-  touch_batch(p, indices, offsets, out, touch_blocks);
+    const void* __restrict__ offsets, void* __restrict__ out, const Touch touch) {
+  touch_batch(p, w, indices, offsets, out, touch);
   const int lane = threadIdx.x & (kWave - 1);
   const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
   const uint64_t g0 = wave * kTileBags;
@@ -625,7 +645,7 @@ static bool one_per_bag(const KParams& p) { return static_cast<uint64_t>(p.N) ==
 template <typename WT, int EPL, int U, bool SIGN>
 static hipError_t launch_tiled_t(const WT* w, const KParams& p, const void* indices,
                                  const void* offsets, void* out, hipStream_t stream,
-                                 uint32_t touch) {
+                                 const Touch& touch) {
   const uint32_t blocks = grid_of((p.num_bags + kTileBags - 1) / kTileBags);
   if (blocks == 0) return hipErrorInvalidConfiguration;
   const dim3 grid(blocks, (p.d + kWave * EPL - 1) / (kWave * EPL));
@@ -637,7 +657,7 @@ static hipError_t launch_tiled_t(const WT* w, const KParams& p, const void* indi
 template <typename WT, bool SIGN>
 static hipError_t launch_tiled(const WT* w, const KParams& p, const void* indices,
                                const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch) {
+                               const Touch& touch) {
   if (p.d <= 64) return launch_tiled_t<WT, 1, 16, SIGN>(w, p, indices, offsets, out, stream, touch);
   if (p.d <= 128) return launch_tiled_t<WT, 2, 8, SIGN>(w, p, indices, offsets, out, stream, touch);
   if (p.d <= 256) return launch_tiled_t<WT, 4, 4, SIGN>(w, p, indices, offsets, out, stream, touch);
@@ -647,7 +667,7 @@ static hipError_t launch_tiled(const WT* w, const KParams& p, const void* indice
 template <typename WT, int V, int LPB, bool SIGN>
 static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indices,
                                 const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch, const KeygenOut& kg) {
+                               const Touch& touch, const KeygenOut& kg) {
   const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? row_batch<V, LPB>() : 1);
   const uint32_t blocks = grid_of((p.num_bags + per_wave - 1) / per_wave);
   if (blocks == 0) return hipErrorInvalidConfiguration;
@@ -664,7 +684,7 @@ static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indic
 template <typename WT, int V, bool SIGN>
 static hipError_t launch_rows_v(const WT* w, const KParams& p, const void* indices,
                                 const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch, const KeygenOut& kg) {
+                               const Touch& touch, const KeygenOut& kg) {
   const uint32_t lanes = (p.d + V - 1) / V;
   if (lanes <= 4) return launch_rows_t<WT, V, 4, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
   if (lanes <= 8) return launch_rows_t<WT, V, 8, SIGN>(w, p, indices, offsets, out, stream, touch, kg);
@@ -688,7 +708,7 @@ static bool tiled_applies(const KParams& p) {
 template <typename WT, bool SIGN>
 static hipError_t launch_fwd_s(const WT* w, const KParams& p, const void* indices,
                                const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch, const KeygenOut& kg) {
+                               const Touch& touch, const KeygenOut& kg) {
   if (tiled_applies<WT>(p)) {
     if (kg.keys != nullptr) return hipErrorInvalidValue;  // it does not write them
     return launch_tiled<WT, SIGN>(w, p, indices, offsets, out, stream, touch);
@@ -700,7 +720,7 @@ static hipError_t launch_fwd_s(const WT* w, const KParams& p, const void* indice
 template <typename WT>
 static hipError_t launch_fwd_w(const WT* w, const KParams& p, const void* indices,
                                const void* offsets, void* out, hipStream_t stream,
-                               uint32_t touch, const KeygenOut& kg) {
+                               const Touch& touch, const KeygenOut& kg) {
   if (p.sign_mode) return launch_fwd_s<WT, true>(w, p, indices, offsets, out, stream, touch, kg);
   return launch_fwd_s<WT, false>(w, p, indices, offsets, out, stream, touch, kg);
 }
@@ -708,7 +728,13 @@ static hipError_t launch_fwd_w(const WT* w, const KParams& p, const void* indice
 hipError_t launch_forward(const void* w, bool bf16, const KParams& p, const void* indices,
                           const void* offsets, void* out, hipStream_t stream, bool batch_read,
                           const KeygenOut& kg) {
-  const uint32_t touch = !batch_read && p.num_bags >= kTouchBags ? kTouchBlocks : 0u;
+  // (bags of several items gain from neither: 26 x 32768 bags of 20 items 906 us
+  // without, 911 us with the array read)
+  Touch touch;
+  touch.index = !batch_read && p.num_bags >= kTouchBags ? 1u : 0u;
+  const uint64_t bytes = static_cast<uint64_t>(p.M) * (bf16 ? 2 : 4);
+  const uint64_t gathered = static_cast<uint64_t>(p.N) * p.d * (bf16 ? 2 : 4);
+  if (bytes > kL2Bytes && bytes <= kTouchMaxBytes && gathered >= 8 * bytes) touch.bytes = bytes;
   if (bf16)
     return launch_fwd_w(static_cast<const uint16_t*>(w), p, indices, offsets, out, stream, touch, kg);
   return launch_fwd_w(static_cast<const float*>(w), p, indices, offsets, out, stream, touch, kg);
