@@ -6,7 +6,7 @@
 // the pair (h0, r): h0 = the item hash of (index, table), equal for equal
 // tokens, and r = b*T + t, the pooled row of its bag; and the tile's counts
 // of h0's low kSortBits bits, the first radix pass's histogram
-// (counts[d * nblocks + tile]).
+// (counts, see count_at).
 #pragma once
 
 #include "pss_kernels.hpp"
@@ -27,6 +27,14 @@ template <bool I32>
 __device__ __forceinline__ int64_t load_int(const void* a, uint64_t i) {
   if constexpr (I32) return static_cast<const int32_t*>(a)[i];
   else return static_cast<const int64_t*>(a)[i];
+}
+
+// Where a sort tile's count of digit d stands: by digit (rows of nblocks
+// tiles), or by tile (rows of kBins digits).
+__device__ __forceinline__ uint64_t count_at(uint32_t d, uint32_t tile, uint32_t nblocks,
+                                             uint32_t by_tile) {
+  return by_tile ? static_cast<uint64_t>(tile) * kBins + d
+                 : static_cast<uint64_t>(d) * nblocks + tile;
 }
 
 // LDS of keygen_process.
@@ -82,7 +90,8 @@ __device__ __forceinline__ void keygen_process(const KParams& p, const void* __r
                                                uint32_t* __restrict__ rows,
                                                float* __restrict__ inv_len,
                                                uint32_t* __restrict__ counts,
-                                               const uint32_t nblocks, const uint32_t tile,
+                                               const uint32_t nblocks, const uint32_t by_tile,
+                                               const uint32_t tile,
                                                const KeygenIn& in, KeygenLds& lds) {
   const int64_t tile0 = static_cast<int64_t>(tile) * kSortTile;
   const int in_tile = p.N - tile0 < kSortTile ? static_cast<int>(p.N - tile0) : kSortTile;
@@ -139,7 +148,7 @@ __device__ __forceinline__ void keygen_process(const KParams& p, const void* __r
     uint32_t c = 0;
 #pragma unroll
     for (int ww = 0; ww < kWavesPerBlock; ++ww) c += lds.hist[ww][d];
-    counts[static_cast<uint64_t>(d) * nblocks + tile] = c;
+    counts[count_at(d, tile, nblocks, by_tile)] = c;
   }
 }
 
