@@ -128,11 +128,16 @@ __device__ __forceinline__ void touch_batch(const KParams& p, const void* __rest
 // reductions.
 // ---------------------------------------------------------------------------
 
-// Items a lane group has in flight: 8 pieces of 16 bytes per lane keep the
-// kernels within 64 VGPRs, 8 wavefronts per SIMD.  16 in flight (half the
-// wavefronts) gained 2% on long bags and lost 15% on short ones; 4 lost 1%
-// on 26 x 65536 rows.
-template <int V, int LPB> constexpr int row_batch() { return LPB >= 8 ? 8 : 4; }
+// Items a lane group of the bags kernel has in flight: 8 pieces of 16 bytes
+// per lane keep it within 64 VGPRs, 8 wavefronts per SIMD.  16 in flight (half the
+// wavefronts) gained 2% on bags of 20 items and lost 15% on shorter ones; 4
+// lost 1% on the long bags.
+template <int LPB> constexpr int bag_batch() { return LPB >= 8 ? 8 : 4; }
+// Rows a lane group of the one-row-per-bag kernel holds: more wavefronts of
+// fewer rows each hide the index load's latency better.  8 / 4 rows: 3328
+// rows of 512 bytes 4.2 / 3.6 us, 26 x 2048 10.7 / 9.2 us, 26 x 65536 183 / 180 us a
+// lookup pass, 401 / 398 us a training step.
+constexpr int kRowBatch = 4;
 
 template <int V> struct Piece;
 template <> struct Piece<4> { typedef f32x4 type; };
@@ -269,7 +274,7 @@ template <typename WT, int V, int LPB, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
     const void* __restrict__ offsets, void* __restrict__ out, const KeygenOut kg) {
-  constexpr int U = row_batch<V, LPB>();
+  constexpr int U = bag_batch<LPB>();
   constexpr int GP = kWave / LPB;
   static_assert(U <= LPB, "one lane per item of the batch");
   __shared__ uint32_t tab_all[kWavesPerBlock][GP * U * LPB];
@@ -360,7 +365,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
 // piece split by the end of the array, works bag by bag.
 //
 // This replaced a persistent kernel that wrote the output in row order, one
-// wavefront per SIMD in groups of 32 steps: 3328 rows of 512 bytes 11.8 -> 4.2 us, 10240
+// wavefront per SIMD in groups of 32 steps: 3328 rows of 512 bytes 11.8 -> 3.6 us, 10240
 // 13 -> 5 us, 26 x 2048 13.1 -> 9 us, 26 x 16384 50.7 -> 45.4 us, 26 x 65536
 // 179 -> 170 us (187 -> 176 us in a training step); and the tiled kernel for d = 16 and
 // 1024 rows 18.1 -> 4.0 us.  Writing the rows alone in table order takes 160-170 us at
@@ -371,7 +376,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_stream_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
     const void* __restrict__ offsets, void* __restrict__ out, const Touch touch,
     const KeygenOut kg) {
-  constexpr int U = row_batch<V, LPB>();
+  constexpr int U = kRowBatch;
   constexpr int GP = kWave / LPB;
   constexpr int NB = U * GP;
   static_assert(NB <= kWave, "one lane per bag");
@@ -668,7 +673,7 @@ template <typename WT, int V, int LPB, bool SIGN>
 static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indices,
                                 const void* offsets, void* out, hipStream_t stream,
                                const Touch& touch, const KeygenOut& kg) {
-  const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? row_batch<V, LPB>() : 1);
+  const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? kRowBatch : 1);
   const uint32_t blocks = grid_of((p.num_bags + per_wave - 1) / per_wave);
   if (blocks == 0) return hipErrorInvalidConfiguration;
   const dim3 grid(blocks, (p.d + LPB * V - 1) / (LPB * V));
