@@ -45,8 +45,10 @@ def test_piece_widths(d, Z, bag):
         _step(Layer(wl, **kw))
 
 
-# (T, B): ends of the pieces of 64, the change to pieces of 256, their ends
-@pytest.mark.parametrize("T,B", [(1, 63), (1, 64), (1, 65), (4, 8192), (1, 32769), (7, 5000)])
+# (T, B): ends of the pieces of 64, the change to pieces of 256, their ends,
+# the most lookups per table and one more (grouped)
+@pytest.mark.parametrize("T,B", [(1, 63), (1, 64), (1, 65), (4, 8192), (3, 10923), (7, 5000),
+                                 (1, 12000), (1, 12001)])
 @pytest.mark.parametrize("prep", ["none", "forward", "explicit"])
 def test_piece_sizes(T, B, prep):
     # 3 rows: every piece is a few long runs over all lane groups
@@ -84,4 +86,4 @@ def test_piece_bags(case, kw):
     else:                       # pieces of 256, bags of 0 .. 7 items
         lengths = list(np.random.default_rng(3).integers(0, 8, 12_000))
     print(f"bags {case} {kw}", flush=True)
-    _step(_with_bags(lengths, 2, **kw))
+    _step(_with_bags(lengths, 4 if case == "big-pieces" else 2, **kw))
