@@ -273,14 +273,15 @@ __device__ __forceinline__ void table_fence() {
 template <typename WT, int V, int LPB, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const KeygenOut kg) {
+    const void* __restrict__ offsets, void* __restrict__ out, const uint64_t wave0,
+    const KeygenOut kg) {
   constexpr int U = bag_batch<LPB>();
   constexpr int GP = kWave / LPB;
   static_assert(U <= LPB, "one lane per item of the batch");
   __shared__ uint32_t tab_all[kWavesPerBlock][GP * U * LPB];
   const int lane = threadIdx.x & (kWave - 1);
   const int grp = lane / LPB, gl = lane % LPB;
-  const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
+  const uint64_t wave = wave0 + xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
   if (wave * GP >= p.num_bags) return;  // whole wavefront
   uint32_t* tab = tab_all[threadIdx.x >> 6] + grp * U * LPB;
   const uint64_t g = wave * GP + grp;
@@ -374,8 +375,8 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
 template <typename WT, int V, int LPB, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads, 8) void forward_stream_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const Touch touch,
-    const KeygenOut kg) {
+    const void* __restrict__ offsets, void* __restrict__ out, const uint64_t wave0,
+    const Touch touch, const KeygenOut kg) {
   constexpr int U = kRowBatch;
   constexpr int GP = kWave / LPB;
   constexpr int NB = U * GP;
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_stream_kernel(
   __shared__ uint32_t tab_all[kWavesPerBlock][NB * LPB];
   const int lane = threadIdx.x & (kWave - 1);
   const int grp = lane / LPB, gl = lane % LPB;
-  const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
+  const uint64_t wave = wave0 + xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
   const uint64_t q0 = wave * NB;
   if (q0 >= p.num_bags) return;  // whole wavefront
   uint32_t* tab = tab_all[threadIdx.x >> 6];
@@ -535,10 +536,11 @@ __device__ __forceinline__ void forward_onehot_tile(
 template <typename WT, int EPL, int U, bool SIGN>
 __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
     const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
-    const void* __restrict__ offsets, void* __restrict__ out, const Touch touch) {
+    const void* __restrict__ offsets, void* __restrict__ out, const uint64_t wave0,
+    const Touch touch) {
   touch_batch(p, w, indices, offsets, out, touch);
   const int lane = threadIdx.x & (kWave - 1);
-  const uint64_t wave = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
+  const uint64_t wave = wave0 + xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
   const uint64_t g0 = wave * kTileBags;
   if (g0 >= p.num_bags) return;
   const uint32_t c0 = blockIdx.y * (kWave * EPL);
@@ -637,12 +639,25 @@ __global__ __launch_bounds__(kBlockThreads) void forward_kernel(
   for (int z = cur + 1; z < tl.nb; ++z) store_row(z, true);
 }
 
-// Workgroups of a grid over `waves` wavefronts: a multiple of kXcds (the
-// extra workgroups lie past the last bag and exit at once); 0 = too many.
-static uint32_t grid_of(uint64_t waves) {
-  const uint64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-  const uint64_t grid = (blocks + kXcds - 1) / kXcds * kXcds;
-  return grid > 0x7fffffffull ? 0u : static_cast<uint32_t>(grid);
+// A grid dimension holds fewer than 2^32 work-items (a larger one is cut to
+// its low 32 bits without an error, and rows stay unwritten): batches of more
+// bags take several launches, of whole multiples of kXcds workgroups.
+constexpr uint64_t kMaxBlocks = 0xffffffffull / kBlockThreads / kXcds * kXcds;
+
+// launch(blocks, wave0, touch) for consecutive shares of `waves` wavefronts, of
+// which the first also reads ahead; blocks is a multiple of kXcds (the extra
+// workgroups of the last share lie past the last bag and exit at once).
+template <typename F>
+static hipError_t launch_shares(uint64_t waves, const Touch& touch, F launch) {
+  const uint64_t all = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+  for (uint64_t b0 = 0; b0 < all; b0 += kMaxBlocks) {
+    const uint64_t n = all - b0 < kMaxBlocks ? all - b0 : kMaxBlocks;
+    launch(static_cast<uint32_t>((n + kXcds - 1) / kXcds * kXcds), b0 * kWavesPerBlock,
+           b0 == 0 ? touch : Touch{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 static bool one_per_bag(const KParams& p) { return static_cast<uint64_t>(p.N) == p.num_bags; }
@@ -651,12 +666,12 @@ template <typename WT, int EPL, int U, bool SIGN>
 static hipError_t launch_tiled_t(const WT* w, const KParams& p, const void* indices,
                                  const void* offsets, void* out, hipStream_t stream,
                                  const Touch& touch) {
-  const uint32_t blocks = grid_of((p.num_bags + kTileBags - 1) / kTileBags);
-  if (blocks == 0) return hipErrorInvalidConfiguration;
-  const dim3 grid(blocks, (p.d + kWave * EPL - 1) / (kWave * EPL));
-  hipLaunchKernelGGL((forward_kernel<WT, EPL, U, SIGN>), grid, dim3(kBlockThreads), 0, stream, w,
-                     p, indices, offsets, out, touch);
-  return hipGetLastError();
+  const uint32_t slabs = (p.d + kWave * EPL - 1) / (kWave * EPL);
+  return launch_shares((p.num_bags + kTileBags - 1) / kTileBags, touch,
+                       [&](uint32_t blocks, uint64_t wave0, const Touch& t) {
+    hipLaunchKernelGGL((forward_kernel<WT, EPL, U, SIGN>), dim3(blocks, slabs),
+                       dim3(kBlockThreads), 0, stream, w, p, indices, offsets, out, wave0, t);
+  });
 }
 
 template <typename WT, bool SIGN>
@@ -674,16 +689,16 @@ static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indic
                                 const void* offsets, void* out, hipStream_t stream,
                                const Touch& touch, const KeygenOut& kg) {
   const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? kRowBatch : 1);
-  const uint32_t blocks = grid_of((p.num_bags + per_wave - 1) / per_wave);
-  if (blocks == 0) return hipErrorInvalidConfiguration;
-  const dim3 grid(blocks, (p.d + LPB * V - 1) / (LPB * V));
-  if (one_per_bag(p))
-    hipLaunchKernelGGL((forward_stream_kernel<WT, V, LPB, SIGN>), grid, dim3(kBlockThreads), 0,
-                       stream, w, p, indices, offsets, out, touch, kg);
-  else
-    hipLaunchKernelGGL((forward_bags_kernel<WT, V, LPB, SIGN>), grid, dim3(kBlockThreads), 0,
-                       stream, w, p, indices, offsets, out, kg);
-  return hipGetLastError();
+  const uint32_t slabs = (p.d + LPB * V - 1) / (LPB * V);
+  return launch_shares((p.num_bags + per_wave - 1) / per_wave, touch,
+                       [&](uint32_t blocks, uint64_t wave0, const Touch& t) {
+    if (one_per_bag(p))
+      hipLaunchKernelGGL((forward_stream_kernel<WT, V, LPB, SIGN>), dim3(blocks, slabs),
+                         dim3(kBlockThreads), 0, stream, w, p, indices, offsets, out, wave0, t, kg);
+    else
+      hipLaunchKernelGGL((forward_bags_kernel<WT, V, LPB, SIGN>), dim3(blocks, slabs),
+                         dim3(kBlockThreads), 0, stream, w, p, indices, offsets, out, wave0, kg);
+  });
 }
 
 template <typename WT, int V, bool SIGN>

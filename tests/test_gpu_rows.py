@@ -8,9 +8,12 @@ kernels, and one-hot batches of 2^20 bags on an array beyond 32 MiB a third.
 """
 import numpy as np
 import pytest
+import torch
 
 import synth
 import parity
+from oracle import pss_oracle as o
+from paper_2207_10731_amd import pss
 from parity import Layer
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +59,67 @@ def test_many_bags(M, bag):
         assert np.array_equal(got.astype(np.float64), ref)
     else:
         parity.check_forward(got, ref, s_abs, 1e-5)
+
+
+def _wide_batch(B, lens_of, idx, flags=0):
+    """Pooled bfloat16 rows of one table, d = Z = 33 (a wavefront per row or
+    four), int32 indices; and the rows of `idx` alone by the oracle."""
+    dev = torch.device("cuda", 0)
+    d = Z = 33
+    M = 100_003
+    w = np.random.default_rng(4).standard_normal(M).astype(np.float32)
+    offsets = torch.zeros(B + 1, dtype=torch.int32, device=dev)
+    torch.cumsum(lens_of(dev), 0, dtype=torch.int32, out=offsets[1:])
+    hp = pss.make_hash_params(2207, num_tables=1, batch=B, num_indices=idx.numel(),
+                              flags=pss.PSS_INDEX_I32 | pss.PSS_ROWS_BF16 | flags)
+    out = torch.full((B, d), float("nan"), dtype=torch.bfloat16, device=dev)
+    pss.pss_forward(torch.from_numpy(w).to(dev), M, Z, d, hp, idx.to(dev), offsets, out)
+    torch.cuda.synchronize()
+
+    def rows(indices):
+        n = len(indices)
+        ref, _ = o.forward64(w, M, Z, d, 1, n, hp.a, hp.b, indices.astype(np.int64), np.arange(n + 1))
+        return torch.from_numpy(ref).to(torch.bfloat16)
+
+    return out, rows
+
+
+# A grid dimension holds fewer than 2^32 work-items: a wavefront per bag (d >
+# 32 in single elements) reaches that at 2^26 bags, four bags per
+# wavefront at 2^28.
+def test_more_bags_than_one_grid():
+    B, n = (1 << 26) + 77, 5000
+    at = np.unique(np.concatenate([np.random.default_rng(1).integers(0, B, n),
+                                   [0, B - 1, B - 77, (1 << 26) - 1, 1 << 26, (1 << 26) - 32,
+                                    (1 << 26) - 33]]))
+    idx = np.random.default_rng(2).integers(0, 1 << 31, len(at)).astype(np.int32)
+    print(f"bags B={B}", flush=True)
+
+    def lens(dev):
+        x = torch.zeros(B, dtype=torch.int32, device=dev)
+        x[torch.from_numpy(at).to(dev)] = 1
+        return x
+
+    out, rows = _wide_batch(B, lens, torch.from_numpy(idx))
+    where = torch.from_numpy(at).to(out.device)
+    assert torch.equal(out[where].cpu(), rows(idx))
+    out[where] = 0
+    for part in out.split(1 << 24):
+        assert not part.view(torch.int16).any()
+    del out
+    torch.cuda.empty_cache()
+
+
+def test_more_rows_than_one_grid():
+    period, reps = 1000, 268_500
+    B = period * reps
+    assert B > 1 << 28
+    idx = np.random.default_rng(3).integers(0, 1 << 31, period).astype(np.int32)
+    print(f"rows B={B}", flush=True)
+    out, rows = _wide_batch(B, lambda dev: torch.ones(B, dtype=torch.int32, device=dev),
+                            torch.from_numpy(idx).cuda().repeat(reps))
+    want = rows(idx).to(out.device)
+    for part in out.view(reps, period, 33).split(20_000):
+        assert (part == want).all()
+    del out
+    torch.cuda.empty_cache()
