@@ -256,13 +256,6 @@ __device__ __forceinline__ uint32_t item_entry(const KParams& p, uint32_t h, uin
       base, add_mod_p(sign_hash0(h, p.s_alpha, p.s_beta), chunk_step(p.a2, j)), p);
 }
 
-// The wavefront's LDS table has been written (or read): order it against
-// the next reads (or writes).
-__device__ __forceinline__ void table_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Any batch: one lane group per bag, items in order.  Lane i < U of the
 // group requests the index of item i of the next batch of U items while this
 // one is gathered.  Measured against the tiled kernel that pooled a tile of
@@ -326,7 +319,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
       const uint32_t h = __shfl(h0, grp * LPB + static_cast<int>(i < U ? i : 0u));
       if (k < n * rl.Cs) tab[k] = item_entry<SIGN>(p, h, rl.j0 + j);
     }
-    table_fence();
+    wave_lds_fence();
     uint32_t ent[U];
     bool split = false;
 #pragma unroll
@@ -350,7 +343,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
       for (int u = 0; u < U; ++u)
         if (static_cast<uint32_t>(u) < n) acc += sign_piece<SIGN>(v[u], ent[u]);
     }
-    table_fence();
+    wave_lds_fence();
     e += n;
     left -= n;
   }
@@ -408,7 +401,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_stream_kernel(
     const uint32_t h = __shfl(h0, static_cast<int>(i < NB ? i : 0u));
     if (k < nb * rl.Cs) tab[k] = item_entry<SIGN>(p, h, rl.j0 + j);
   }
-  table_fence();
+  wave_lds_fence();
   uint32_t ent[U];
   bool odd = mine && !(o0 == static_cast<int64_t>(g) && o1 == static_cast<int64_t>(g) + 1);
 #pragma unroll

@@ -147,6 +147,14 @@ __device__ __forceinline__ uint32_t readlane_u32(uint32_t v, int lane) {
   return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), lane));
 }
 
+// Orders the wavefront's LDS writes before it against its LDS reads after it
+// (and reads before writes) where lanes exchange values: no instruction, but
+// nothing may be moved across.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Per-wavefront view of one tile of bags.
 struct Tile {
   uint64_t g0;        // first bag

@@ -281,8 +281,11 @@ __global__ __launch_bounds__(kTileThreads, 5) void tile_apply_kernel(
             x4[v] = off[v] < rlen ? sums[static_cast<uint64_t>(at[v]) + k] : 0.f;
           }
 #pragma unroll
-          for (int v = 0; v < kTileBatch; ++v)
+          for (int v = 0; v < kTileBatch; ++v) {
             if (off[v] < rlen) mine[off[v]] += x4[v];
+            // chunks of two records may overlap at other lanes' elements
+            wave_lds_fence();
+          }
         }
       }
     }

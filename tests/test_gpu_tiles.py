@@ -74,3 +74,16 @@ def test_tile_limits(T, B, M):
     wl = C2.scaled(T=T, B=B, d=16, Z=16, M=M, cardinality="fixed:3" if M < 100_000 else "fixed:9000")
     print(f"tile limits T={T} B={B} M={M}", flush=True)
     _check(wl)
+
+
+# As many records per tile as the rule takes, so that most chunks of a range
+# overlap others at other bases (other lanes of the group then add to an element
+# that a lane has just added to): elements covered 4 to 256 times.
+@pytest.mark.parametrize("d,Z", [(16, 16), (32, 8), (64, 64), (36, 12), (256, 256), (1024, 1024)])
+def test_tile_overlaps(d, Z):
+    tiles = 3
+    T, B = 1, 1024 * tiles * Z // d
+    wl = C2.scaled(T=T, B=B, d=d, Z=Z, M=tiles * 4096 - 5, cardinality="fixed:1000000",
+                   optimizer="adagrad")
+    print(f"tile overlaps d={d} Z={Z}", flush=True)
+    _check(wl)
