@@ -170,8 +170,8 @@ enum {
  *           each token's sum is added once at its hashed addresses (float
  *           atomics; a token whose lookups span several of the 256-pair
  *           pieces of the grouped order adds one partial sum per piece).
- *           Small batches are not sorted first: their pieces of 64 or 256
- *           lookups are taken in the batch's own order.
+ *           Small one-hot batches take one kernel, whose pieces of 64 or
+ *           128 lookups each workgroup finds by itself.
  *   SPARSE  Alg. 1 sparse branch: the unique locations and summed values of
  *           pss_gradient_sparse, then the optimizer applied at those
  *           locations only.  No float atomics: bit-identical run to run.

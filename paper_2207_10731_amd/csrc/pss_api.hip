@@ -259,9 +259,9 @@ class CallScratch {
 // For some batches the forward call makes the grouping's first stage (keygen)
 // on the caller's stream instead (`fused`: no side stream, no events): the
 // forward kernel itself for a small batch, whose backward takes the keygen as
-// it is (deposits_by_piece); a kernel ahead of it, with the first radix pass's
-// digit counts, for a large one with as many items as bags, whose backward
-// finishes the grouping.
+// it is (deposits_by_piece) or finishes the grouping; a kernel ahead of it, with
+// the first radix pass's digit counts, for a large one with as many items as
+// bags, whose backward finishes the grouping.
 struct Prepared {
   std::mutex mu;
   hipStream_t side = nullptr;
@@ -467,6 +467,11 @@ Prepared* take_prepared(hipStream_t stream, const void* indices, const void* off
 }
 
 int hip_status(hipError_t st) { return st == hipSuccess ? PSS_OK : PSS_ERR_HIP; }
+
+// Lookups of a batch of several items per bag whose keygen the forward kernel
+// writes: a small batch's forward has time to spare for it, and the events of a
+// side stream cost more than the grouping.
+constexpr int64_t kForwardKeygenItems = 1 << 18;
 
 // Whether a backward with these flags can run the SORTED variant grouped by
 // token (the grouping that pss_prepare_backward makes ahead): AUTO or SORTED,
@@ -691,11 +696,14 @@ int pss_forward(const void* shared, int64_t M, int32_t Z, int32_t d,
     // small batches: the forward kernel writes the keygen; large ones with as
     // many items as bags: a kernel ahead of it, with digit counts; others are
     // grouped on the library stream beside it (26 x 32768 bags of 20 items: step
-    // 3128 us, with the keygen written by the forward kernel 3193 us)
-    const bool by_piece =
-        pss::deposits_by_piece(p) && !(hash_params->flags & PSS_DEPOSIT_BY_ADDRESS);
-    ahead = !by_piece && pss::keygen_counts(p);
-    if (by_piece || ahead) {
+    // 3128 us, with the keygen written by the forward kernel 3193 us; 13 x 1000 bags of
+    // 9 items 72 us, 50 us)
+    const bool by_address = (hash_params->flags & PSS_DEPOSIT_BY_ADDRESS) != 0;
+    const bool one_each = pss::keygen_counts(p);
+    const bool by_forward =
+        !by_address && (one_each ? pss::deposits_by_piece(p) : p.N <= kForwardKeygenItems);
+    ahead = !by_forward && one_each;
+    if (by_forward || ahead) {
       if (prepare_fused(p, indices, offsets, stream, &kg, &fused) != PSS_OK) {
         (void)hipGetLastError();
         fused = nullptr;

@@ -23,8 +23,8 @@ struct KeygenOut {
 // float32 (bfloat16 when p.rows_bf16).  batch_read: the work just enqueued on
 // the stream has read indices and offsets (they are in the caches).  With
 // kg.keys the kernel also writes the lookups' keys, rows and inv_len there (no
-// digit counts; only where keygen_counts or deposits_by_piece sends it: the
-// tiled kernel, which meets neither, does not write them).
+// digit counts; batches of fewer than 2^20 bags only: the tiled kernel does not
+// write them).
 hipError_t launch_forward(const void* w, bool bf16, const KParams& p, const void* indices,
                           const void* offsets, void* out, hipStream_t stream, bool batch_read,
                           const KeygenOut& kg);
@@ -66,10 +66,10 @@ hipError_t launch_group_sorted(const KParams& p, const void* indices, const void
 void set_reduce_events(hipEvent_t before, hipEvent_t after);
 void reduce_events(hipEvent_t* before, hipEvent_t* after);  // both or neither
 
-// The sorted deposit of a small batch in one kernel, grouped within pieces of
-// consecutive lookups (deposits_by_piece: whether it is the faster form).
-// With pairs (the keygen of this batch: keys, rows and inv_len in item order)
-// indices and offsets are not read.
+// The sorted deposit of a small one-hot batch in one kernel, by pieces of the order by
+// token (deposits_by_piece: whether it is the faster form).  With pairs
+// (the keygen of this batch: keys, rows and inv_len in item order) indices and
+// offsets are not read.
 bool deposits_by_piece(const KParams& p);
 hipError_t launch_deposit_pieces(float* dst, float scale, const KParams& p, const void* indices,
                                  const void* offsets, const GroupedPairs* pairs, const void* grad,
@@ -80,10 +80,11 @@ hipError_t launch_reduce_sorted(float* dst, float scale, const KParams& p, const
 
 // The same pieces' run sums as records instead: rows of `sums` (N x d floats)
 // and N * C (base, row * C + j) records, base 0xffffffff where there is none.
-// Requires p.N * p.C < 2^32.
+// Requires p.N * p.C < 2^32 and pieces_fit; pairs may be null with keygen_counts.
+bool pieces_fit(const KParams& p);
 hipError_t launch_piece_records(float* sums, const KParams& p, const void* indices,
-                                const void* offsets, const void* grad, uint32_t* rec_keys,
-                                uint32_t* rec_ids, hipStream_t stream);
+                                const void* offsets, const GroupedPairs* pairs, const void* grad,
+                                uint32_t* rec_keys, uint32_t* rec_ids, hipStream_t stream);
 
 // Sparse gradient and update of a small batch by array tile (sparse_by_tile:
 // whether it applies); the same results as launch_gradient_sparse and

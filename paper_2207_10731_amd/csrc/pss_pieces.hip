@@ -1,17 +1,13 @@
-// Deposit by pieces: the SORTED backward of small batches in one kernel.
+// Deposit by pieces: the SORTED backward of small one-hot batches in one kernel.
 //
 // The grouped deposit (radix sort of the lookups by token, then the reduce
 // stage) is a chain of four or five launches.  Up to kPieceMaxItems lookups that chain, not
-// the memory traffic, is most of the call's time.  Here a workgroup takes P
-// consecutive lookups in the batch's own order (items of one table, usually), finds
-// their bags, sorts them by item hash, sums the output-gradient rows of each
-// token and adds each sum once at its hashed addresses.  A token is deposited
-// once per piece that holds it instead of about once per batch: 1.6 times the
-// deposits on 26 x 2048 Zipf(1.1) lookups in pieces of 256.
+// the memory traffic, is most of the call's time.  Here a workgroup finds by
+// itself the lookups of one piece of the order by token (token_order), sorts them
+// by item hash, sums the output-gradient rows of each token and adds each
+// sum once at its hashed addresses.
 //
-//   items   item -> (h0, row, 1/|bag|): its bag is the item's own position
-//           in a one-hot piece, else found by a search over the offsets; or
-//           read from a prepared keygen (keys, rows)
+//   order   lookups of the piece: see token_order
 //   sort    by counting, 4 threads per pair
 //   sum     groups of LPB lanes (lanes over the dims), each 16 (LPB = 64), 8
 //           or 4 consecutive pairs of the merged order, all rows requested
@@ -19,6 +15,13 @@
 //           pairs is finished by the group where it began
 //   deposit float atomics at the run's chunk entries (hashed once per pair
 //           into LDS for C <= kTabChunks)
+//
+// Pieces of the batch's own order, each token deposited once per piece that holds
+// it, need no order stage, but every deposit rounds in 32 bits at its element: the
+// distance from 64-bit sums grew up to 1.5 times (2 tables of 3927
+// Zipf lookups, d = 256, Z = 8).  In the order by token it is 0.63 to 1.02 times
+// the grouped deposit's, shape by shape (a single token alone, whose distance differs
+// 0.8 to 1.8 times between two runs, apart).
 #include <hip/hip_ext.h>
 
 #include "pss_keygen.hpp"
@@ -26,21 +29,247 @@
 
 namespace pss {
 
-// Largest g in [0, num_bags) with offsets[g] <= e (0 if none), by one
-// wavefront: 64 probes per step.
+// The bag of lookup e: largest g with offsets[g] <= e.
 template <bool I32>
-__device__ __forceinline__ uint64_t bag_search(const void* __restrict__ offsets, uint64_t num_bags,
-                                               int64_t e, int lane) {
-  uint64_t lo = 0, hi = num_bags;
-  while (hi - lo > 1) {
-    const uint64_t step = (hi - lo + kWave - 1) / kWave;
-    const uint64_t pos = lo + (static_cast<uint64_t>(lane) + 1) * step;
-    const bool below = pos < hi && load_int<I32>(offsets, pos) <= e;
-    const uint64_t n = static_cast<uint64_t>(__popcll(__ballot(below)));
-    lo += n * step;
-    hi = lo + step < hi ? lo + step : hi;
+__device__ __forceinline__ uint64_t bag_of(const KParams& p, const void* __restrict__ offsets,
+                                           int64_t e) {
+  uint64_t lo = 0, hi = p.num_bags - 1;
+  while (lo < hi) {
+    const uint64_t mid = (lo + hi + 1) >> 1;
+    if (load_int<I32>(offsets, mid) <= e) lo = mid; else hi = mid - 1;
   }
   return lo;
+}
+
+// The order by token: the batch is cut into regions of `len` consecutive lookups
+// (whole tables), a region into `pieces` pieces of its lookups ordered by bins of
+// the item hash, within a bin as in the batch.  Every workgroup counts its region's
+// bins by itself (their keys stay in LDS), finds the piece's two cuts and collects
+// the lookups between them: no sorted list is kept, and no launch is needed to make
+// one.  A token is then deposited once, or once per piece of a bin that outgrows the
+// slack below, as in the grouped deposit.  The cost grows with the region:
+// see kPieceRegion.
+//
+// Nominal cuts lie piece_cut apart; a cut inside a bin of up to P - piece_cut lookups
+// moves back to the bin's start, so that no small bin is divided, and a piece
+// has at most P lookups.
+struct Regions {
+  uint32_t len, pieces;
+};
+constexpr int kTokenBins = 1024;
+template <int P> constexpr uint32_t piece_cut() { return P - P / 8; }
+__device__ __forceinline__ uint32_t token_bin(uint32_t key) { return (key * 0x9e3779b1u) >> 22; }
+
+template <int P>
+struct TokenOrder {
+  static constexpr int kWaves = 4 * P / kWave;
+  __align__(16) uint64_t pair[P];  // the piece's lookups, in any order: key << 32 | lookup
+  uint32_t start[kTokenBins];      // counts, then first position of each bin
+  uint32_t wsum[kWaves], part[2][kWaves];
+  uint32_t cut[2], bin[2];         // the piece's cuts and the bins they divide
+  uint32_t taken;
+  int irregular;
+};
+constexpr uint32_t kNoBin = 0xffffffffu;
+
+// Collects the lookups of workgroup blockIdx.x's piece in lds.pair, sets *p0 to its first
+// position in the batch and returns their number (the same for the whole
+// workgroup).  Which lookups they are depends on the batch alone.
+template <int P, bool I32>
+__device__ __forceinline__ int token_order(const KParams& p, const void* __restrict__ indices,
+                                           const void* __restrict__ offsets,
+                                           const uint32_t* __restrict__ keys, const Regions& regions,
+                                           TokenOrder<P>& lds, uint32_t* p0, bool* searched) {
+  constexpr int NT = 4 * P, NW = TokenOrder<P>::kWaves;
+  constexpr uint32_t kCut = piece_cut<P>(), kSlack = P - kCut;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
+  const uint32_t region = blockIdx.x / regions.pieces, piece = blockIdx.x - region * regions.pieces;
+  const uint32_t lo = region * regions.len;  // N < 2^32
+  const uint32_t n = static_cast<uint32_t>(p.N) - lo < regions.len ? static_cast<uint32_t>(p.N) - lo
+                                                                  : regions.len;
+  const uint32_t q0 = piece * kCut, q1 = q0 + kCut < n ? q0 + kCut : n;  // nominal cuts
+  if (q0 >= n) return 0;
+  // a wavefront takes a contiguous part of the region, in whole wavefronts
+  const uint32_t per_wave = ((n + NW - 1) / NW + kWave - 1) / kWave * kWave;
+  const uint32_t i_lo = w * per_wave < n ? w * per_wave : n;
+  const uint32_t i_hi = i_lo + per_wave < n ? i_lo + per_wave : n;
+  extern __shared__ uint32_t region_keys[];  // n, kept between the passes
+  bool search = false;  // bags are not one item each: found by a search
+  for (;;) {
+    for (int b = tid; b < kTokenBins; b += NT) lds.start[b] = 0;
+    if (tid == 0) lds.irregular = 0;
+    __syncthreads();
+    // without keys: as many lookups as bags, one per bag unless an offset says
+    // otherwise (then e < num_bags all over the region)
+    const bool check = keys == nullptr && !search;
+    bool odd = check && tid == 0 && load_int<I32>(offsets, lo + n) != lo + n;
+    constexpr int kAhead = 8;  // requested together
+    for (uint32_t i0 = i_lo; i0 < i_hi; i0 += kAhead * kWave) {
+      uint32_t e[kAhead], k[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {  // (past the end: the last one again)
+        const uint32_t i = i0 + u * kWave + lane;
+        e[u] = lo + (i < i_hi ? i : i_hi - 1);
+      }
+      if (keys != nullptr) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) k[u] = keys[e[u]];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) k[u] = k[u] < kP ? k[u] : 0u;
+      } else {
+        uint32_t g[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          k[u] = static_cast<uint32_t>(load_int<I32>(indices, e[u]));
+          g[u] = static_cast<uint32_t>(load_int<I32>(offsets, e[u]));  // at most N < 2^32
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) odd |= check && g[u] != e[u];
+        if (search) {
+#pragma unroll 1
+          for (int u = 0; u < kAhead; ++u) {
+            const uint32_t b = static_cast<uint32_t>(bag_of<I32>(p, offsets, e[0] + u * kWave));
+#pragma unroll
+            for (int v = 0; v < kAhead; ++v) g[v] = u == v ? b : g[v];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          k[u] = item_hash(k[u], (search ? g[u] : e[u]) / p.B * p.C, p.TC, p.a, p.b);
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const uint32_t i = i0 + u * kWave + lane;
+        if (i >= i_hi) continue;
+        region_keys[i] = k[u];
+        atomicAdd(&lds.start[token_bin(k[u])], 1u);
+      }
+    }
+    if (odd) lds.irregular = 1;
+    __syncthreads();
+    if (!lds.irregular) break;
+    __syncthreads();
+    search = true;
+  }
+  // positions of the bins, and the two cuts
+  constexpr int kOwn = kTokenBins / NT;  // consecutive bins per thread
+  uint32_t c[kOwn], sum = 0;
+#pragma unroll
+  for (int b = 0; b < kOwn; ++b) {
+    c[b] = lds.start[tid * kOwn + b];
+    sum += c[b];
+  }
+  uint32_t incl = sum;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
+  }
+  if (lane == kWave - 1) lds.wsum[w] = incl;
+  if (tid < 2) {
+    lds.cut[tid] = tid ? q1 : q0;
+    lds.bin[tid] = kNoBin;
+  }
+  if (tid == 2) lds.taken = 0;
+  __syncthreads();
+  uint32_t s = incl - sum;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) s += v < w ? lds.wsum[v] : 0u;
+#pragma unroll
+  for (int b = 0; b < kOwn; ++b) {
+    lds.start[tid * kOwn + b] = s;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const uint32_t q = x ? q1 : q0;
+      if (s < q && q < s + c[b]) {  // the cut lies inside the bin
+        if (c[b] <= kSlack) lds.cut[x] = s;
+        else lds.bin[x] = tid * kOwn + b;
+      }
+    }
+    s += c[b];
+  }
+  __syncthreads();
+  const uint32_t c0 = lds.cut[0], c1 = lds.cut[1];
+  const uint32_t b0 = lds.bin[0], b1 = lds.bin[1];
+  // Slots: the lookups of whole bins as they come, then those of the divided
+  // bins by their position.
+  const uint32_t cnt = c1 - c0;
+  const uint32_t s0 = b0 != kNoBin ? lds.start[b0] : 0u, s1 = b1 != kNoBin ? lds.start[b1] : 0u;
+  uint32_t end0 = c0;  // of b0's part
+  if (b0 != kNoBin) end0 = b0 == b1 || b0 + 1 == kTokenBins ? c1 : lds.start[b0 + 1];
+  const uint32_t n0 = end0 - c0, n1 = b1 != kNoBin && b1 != b0 ? c1 - s1 : 0u;
+  const uint32_t at0 = cnt - n0 - n1, at1 = cnt - n1;
+  const uint64_t below = (1ull << lane) - 1;
+  auto put = [&](uint32_t at, uint32_t k, uint32_t i) {
+    if (at < P) lds.pair[at] = static_cast<uint64_t>(k) << 32 | (lo + i);
+  };
+  constexpr int kSteps = 4;  // looked up together
+  for (uint32_t i0 = i_lo; i0 < i_hi; i0 += kSteps * kWave) {
+    uint32_t k[kSteps], first[kSteps];
+    bool take[kSteps];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      const uint32_t i = i0 + u * kWave + lane;
+      k[u] = i < i_hi ? region_keys[i] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) first[u] = lds.start[token_bin(k[u])];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      const uint32_t b = token_bin(k[u]);
+      take[u] = i0 + u * kWave + lane < i_hi && first[u] >= c0 && first[u] < c1 && b != b0 && b != b1;
+    }
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      const uint64_t m = __ballot(take[u]);
+      if (m == 0) continue;
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&lds.taken, static_cast<uint32_t>(__popcll(m)));
+      base = readlane_u32(base, 0);
+      if (take[u]) put(base + __popcll(m & below), k[u], i0 + u * kWave + lane);
+    }
+  }
+  if (n0 + n1 != 0) {  // ranks in the divided bins, in the batch's order
+    auto each = [&](auto f) {
+      for (uint32_t i0 = i_lo; i0 < i_hi; i0 += kWave) {
+        const uint32_t i = i0 + lane;
+        const uint32_t k = i < i_hi ? region_keys[i] : 0u;
+        const uint32_t b = i >= i_hi ? kNoBin : token_bin(k);
+        f(i, k, __ballot(n0 != 0 && b == b0), __ballot(n1 != 0 && b == b1));
+      }
+    };
+    uint32_t rank0 = 0, rank1 = 0;
+    each([&](uint32_t, uint32_t, uint64_t m0, uint64_t m1) {
+      rank0 += __popcll(m0);
+      rank1 += __popcll(m1);
+    });
+    if (lane == 0) {
+      lds.part[0][w] = rank0;
+      lds.part[1][w] = rank1;
+    }
+    __syncthreads();
+    rank0 = rank1 = 0;
+    for (int v = 0; v < w; ++v) {
+      rank0 += lds.part[0][v];
+      rank1 += lds.part[1][v];
+    }
+    each([&](uint32_t i, uint32_t k, uint64_t m0, uint64_t m1) {
+      if ((m0 >> lane) & 1u) {
+        const uint32_t pos = s0 + rank0 + __popcll(m0 & below);
+        if (pos >= c0 && pos < end0) put(at0 + pos - c0, k, i);
+      }
+      if ((m1 >> lane) & 1u) {
+        const uint32_t pos = s1 + rank1 + __popcll(m1 & below);
+        if (pos < c1) put(at1 + pos - s1, k, i);
+      }
+      rank0 += __popcll(m0);
+      rank1 += __popcll(m1);
+    });
+  }
+  __syncthreads();
+  *p0 = lo + c0;
+  *searched = search;
+  return cnt < P ? static_cast<int>(cnt) : P;
 }
 
 // With REC nothing is deposited: the run that begins at merged position q
@@ -54,123 +283,73 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
     float* __restrict__ dst, const float scale, const KParams p, const void* __restrict__ indices,
     const void* __restrict__ offsets, const uint32_t* __restrict__ keys,
     const uint32_t* __restrict__ rows, const float* __restrict__ inv_len,
-    const GT* __restrict__ grad, uint32_t* __restrict__ rec_keys, uint32_t* __restrict__ rec_ids) {
+    const GT* __restrict__ grad, uint32_t* __restrict__ rec_keys, uint32_t* __restrict__ rec_ids,
+    const Regions regions) {
   constexpr int GP = kWave / LPB;           // lane groups of a wavefront
   constexpr int NG = 4 * P / kWave * GP;    // ... of the workgroup
   constexpr int S = P / NG;                 // pairs per group
   constexpr int U = EPL * S > 64 ? 64 / EPL : S;  // rows in flight
   static_assert(S * GP == 16 && (EPL == 1 || LPB == kWave), "whole rows per group");
-  __shared__ __align__(16) uint32_t lk[P];
   __shared__ uint32_t lr[P], mk[P], mr[P];
   __shared__ float ll[P], ml[P];
-  __shared__ int64_t st[P + 1];
-  __shared__ uint64_t first_bag;
-  __shared__ int irregular;
   __shared__ uint32_t tab[P * kTabChunks];
   __shared__ float headv[NG][EPL * LPB];
   __shared__ uint32_t through[NG];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
-  const int64_t p0 = static_cast<int64_t>(blockIdx.x) * P;
-  const int cnt = p.N - p0 < P ? static_cast<int>(p.N - p0) : P;
-
-  // items
-  const int64_t e = p0 + tid;
-  const bool mine = tid < cnt;
-  uint32_t key = 0xffffffffu, row = 0;
-  float il = 1.f;
-  if (keys != nullptr) {
-    if (mine) {
-      key = keys[e];
-      row = rows[e];
-      // both come from a keygen; the clamps keep reads and ranks in bounds
-      if (key >= kP) key = 0;
-      if (row >= p.num_bags) row = 0;
-      if (p.mean) il = inv_len[row];
-    }
-  } else {
-    uint32_t ix = 0;
-    if (mine) ix = static_cast<uint32_t>(load_int<I32>(indices, static_cast<uint64_t>(e)));
-    // one item per bag: offsets[e] = e all over the piece (then e < num_bags)
-    bool own = static_cast<uint64_t>(p.N) == p.num_bags;
-    if (own && tid <= cnt) own = load_int<I32>(offsets, static_cast<uint64_t>(e)) == e;
-    if (tid == 0) irregular = 0;
-    __syncthreads();
-    if (tid <= cnt && !own) irregular = 1;
-    __syncthreads();
-    uint64_t g = static_cast<uint64_t>(e);
-    if (irregular) {
-      if (w == 0) {
-        const uint64_t g0 = bag_search<I32>(offsets, p.num_bags, p0, lane);
-        if (lane == 0) first_bag = g0;
-      }
-      __syncthreads();
-      const uint64_t g0 = first_bag;
-      if (tid <= P) {
-        const uint64_t q = g0 + tid < p.num_bags ? g0 + tid : p.num_bags;
-        st[tid] = load_int<I32>(offsets, q);
-      }
-      __syncthreads();
-      if (mine) {
-        int64_t s0, s1;
-        // the P bags from g0 on reach the piece's last item, unless many
-        // of them are empty
-        if (g0 + P >= p.num_bags || st[P] > p0 + cnt - 1) {
-          const int nb = p.num_bags - g0 < P ? static_cast<int>(p.num_bags - g0) : P;
-          int lo = 0;
-          for (int step = P / 2; step >= 1; step >>= 1)
-            if (lo + step < nb && st[lo + step] <= e) lo += step;
-          g = g0 + lo;
-          s0 = st[lo];
-          s1 = st[lo + 1];
-        } else {
-          uint64_t lo = g0, hi = p.num_bags - 1;
-          while (lo < hi) {
-            const uint64_t mid = (lo + hi + 1) >> 1;
-            if (load_int<I32>(offsets, mid) <= e) lo = mid; else hi = mid - 1;
-          }
-          g = lo;
-          s0 = load_int<I32>(offsets, lo);
-          s1 = load_int<I32>(offsets, lo + 1);
-        }
-        if (p.mean && s1 > s0) il = 1.f / static_cast<float>(s1 - s0);
-      }
-    }
-    if (mine) {
-      const uint32_t t = static_cast<uint32_t>(g) / p.B;  // bags number below 2^32
-      const uint32_t b = static_cast<uint32_t>(g) - t * p.B;
-      row = b * p.T + t;
-      key = item_hash(ix, t * p.C, p.TC, p.a, p.b);
-    }
-  }
-
-  // sort, by counting: 4 threads per pair each compare its key with a
-  // quarter of the keys (equal keys keep their order).  Empty slots hold key
-  // 0xffffffff, above any hash, and stay behind.
+  // the piece's lookups
+  __shared__ TokenOrder<P> order;
+  uint32_t p0 = 0;
+  bool searched = false;
+  const int cnt = token_order<P, I32>(p, indices, offsets, keys, regions, order, &p0, &searched);
+  if (cnt == 0) return;  // whole workgroup
+  // their pooled rows and 1/|bag|; empty slots sort last (no key is 0xffffffff)
   if (tid < P) {
-    lk[tid] = key;
+    uint32_t row = 0;
+    float il = 1.f;
+    if (tid >= cnt) {
+      order.pair[tid] = ~0ull;
+    } else {
+      uint32_t e = static_cast<uint32_t>(order.pair[tid]);
+      if (e >= p.N) e = 0;  // (indices changed during the call)
+      if (keys != nullptr) {
+        row = rows[e];
+        if (row >= p.num_bags) row = 0;  // from a keygen; the clamp keeps reads in bounds
+        if (p.mean) il = inv_len[row];
+      } else {
+        uint32_t g = e;
+        if (searched) {
+          g = static_cast<uint32_t>(bag_of<I32>(p, offsets, e));
+          const int64_t o0 = load_int<I32>(offsets, g);
+          const int64_t o1 = load_int<I32>(offsets, static_cast<uint64_t>(g) + 1);
+          if (p.mean && o1 > o0) il = 1.f / static_cast<float>(o1 - o0);
+        }
+        const uint32_t t = g / p.B, b = g - t * p.B;  // bags number below 2^32
+        row = b * p.T + t;
+      }
+    }
     lr[tid] = row;
     ll[tid] = il;
   }
   __syncthreads();
+
+  // sort by key and lookup, by counting: 4 threads per pair each compare it
+  // with a quarter of the pairs
   {
     const int i = tid >> 2, part = tid & 3;
-    const uint32_t ki = lk[i];
+    const uint64_t ki = order.pair[i];
     uint32_t before = 0;
-    const uint4* quarter = reinterpret_cast<const uint4*>(lk + part * (P / 4));
-#pragma unroll 4
-    for (int v = 0; v < P / 16; ++v) {
-      const uint4 k4 = quarter[v];
-      const int j = part * (P / 4) + v * 4;
-      before += k4.x < ki + (j < i ? 1u : 0u);
-      before += k4.y < ki + (j + 1 < i ? 1u : 0u);
-      before += k4.z < ki + (j + 2 < i ? 1u : 0u);
-      before += k4.w < ki + (j + 3 < i ? 1u : 0u);
+    const ulonglong2* quarter = reinterpret_cast<const ulonglong2*>(order.pair + part * (P / 4));
+#pragma unroll 8
+    for (int v = 0; v < P / 8; ++v) {
+      const ulonglong2 k2 = quarter[v];
+      before += k2.x < ki;
+      before += k2.y < ki;
     }
     before += __shfl_xor(before, 1);
     before += __shfl_xor(before, 2);
     const uint32_t rank = i < cnt ? before : static_cast<uint32_t>(i);
     if (part == 0) {
-      mk[rank] = ki;
+      mk[rank] = static_cast<uint32_t>(ki >> 32);
       mr[rank] = lr[i];
       ml[rank] = ll[i];
     }
@@ -323,6 +502,15 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
   }
 }
 
+// Lookups of a region: one item per bag, whole tables of at least 1024 lookups together
+// (smaller ones would leave the last piece of each mostly empty); else the whole
+// batch, whose tables begin where only the device knows.
+static uint32_t region_len(const KParams& p) {
+  if (!keygen_counts(p)) return static_cast<uint32_t>(p.N);
+  const uint64_t tables = (1024 + static_cast<uint64_t>(p.B) - 1) / p.B;
+  return static_cast<uint32_t>(p.B * (tables < p.T ? tables : p.T));
+}
+
 // What a launch writes besides dst: nothing, or records.
 struct PieceRecords {
   uint32_t* keys = nullptr;
@@ -333,33 +521,39 @@ template <int EPL, int LPB, int P, bool SIGN, bool REC, typename GT>
 static hipError_t launch_pieces_t(float* dst, float scale, const KParams& p, const void* indices,
                                   const void* offsets, const GroupedPairs* pairs, const GT* grad,
                                   const PieceRecords& rec, hipStream_t stream) {
-  const dim3 grid(static_cast<uint32_t>((p.N + P - 1) / P), (p.d + LPB * EPL - 1) / (LPB * EPL));
+  Regions regions;
+  regions.len = region_len(p);
+  regions.pieces = (regions.len + piece_cut<P>() - 1) / piece_cut<P>();
+  const uint64_t count = (static_cast<uint64_t>(p.N) + regions.len - 1) / regions.len;
+  const dim3 grid(static_cast<uint32_t>(count * regions.pieces), (p.d + LPB * EPL - 1) / (LPB * EPL));
   const uint32_t* keys = pairs != nullptr ? pairs->keys : nullptr;
   const uint32_t* rows = pairs != nullptr ? pairs->rows : nullptr;
   const float* il = pairs != nullptr ? pairs->inv_len : nullptr;
   const dim3 block(4 * P);
+  const uint32_t lds = regions.len * 4;  // the region's keys
   hipEvent_t before = nullptr, after = nullptr;
   if (!REC) reduce_events(&before, &after);
   const auto kernel = p.idx32 ? deposit_pieces_kernel<EPL, LPB, P, SIGN, true, REC, GT>
                               : deposit_pieces_kernel<EPL, LPB, P, SIGN, false, REC, GT>;
   if (before != nullptr)  // the timing hook: the dispatch records both events
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, before, after, 0u, dst, scale, p, indices,
-                          offsets, keys, rows, il, grad, rec.keys, rec.ids);
+    hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, before, after, 0u, dst, scale, p, indices,
+                          offsets, keys, rows, il, grad, rec.keys, rec.ids, regions);
   else
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, dst, scale, p, indices, offsets, keys, rows,
-                       il, grad, rec.keys, rec.ids);
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, dst, scale, p, indices, offsets, keys, rows,
+                       il, grad, rec.keys, rec.ids, regions);
   return hipGetLastError();
 }
 
-// Pieces of 64 lookups while pieces of 256 would leave compute units idle:
-// 10240 lookups 10.7 / 16 us (64 / 256), 13312 10.4 / 15 us, 53248 32.5 / 28 us (the
-// shorter pieces make more deposits).
-constexpr int64_t kSmallPieceItems = 1 << 15;
-
+// Pieces of 64 lookups for short regions, of 128 for longer ones, whose scan fewer
+// workgroups then repeat.  Backward, 64 / 128 (N lookups in regions of R): N = R = 1024 13.2 / 14.2 us,
+// 26 x 1024 18.3 / 21.5 us, 26 x 2048 28.7 / 28.3 us, N = R = 4096 20.4 / 17.4 us, 13 x 4096
+// 31.4 / 27.7 us.  256: N = R = 4096 21.0 us, 26 x 2048 35.7 us.
+constexpr uint32_t kSmallPieceRegion = 2048;
 template <int EPL, int LPB, bool SIGN, bool REC, typename GT, typename... A>
 static hipError_t launch_pieces_p(float* dst, float scale, const KParams& p, A... a) {
-  if (p.N <= kSmallPieceItems) return launch_pieces_t<EPL, LPB, 64, SIGN, REC, GT>(dst, scale, p, a...);
-  return launch_pieces_t<EPL, LPB, 256, SIGN, REC, GT>(dst, scale, p, a...);
+  if (region_len(p) <= kSmallPieceRegion)
+    return launch_pieces_t<EPL, LPB, 64, SIGN, REC, GT>(dst, scale, p, a...);
+  return launch_pieces_t<EPL, LPB, 128, SIGN, REC, GT>(dst, scale, p, a...);
 }
 
 template <bool SIGN, bool REC, typename GT, typename... A>
@@ -392,35 +586,39 @@ hipError_t launch_deposit_pieces(float* dst, float scale, const KParams& p, cons
 }
 
 hipError_t launch_piece_records(float* sums, const KParams& p, const void* indices,
-                                const void* offsets, const void* grad, uint32_t* rec_keys,
-                                uint32_t* rec_ids, hipStream_t stream) {
+                                const void* offsets, const GroupedPairs* pairs, const void* grad,
+                                uint32_t* rec_keys, uint32_t* rec_ids, hipStream_t stream) {
   const PieceRecords rec{rec_keys, rec_ids};
   if (p.rows_bf16)
-    return launch_pieces_g<true, uint16_t>(sums, 1.f, p, indices, offsets, nullptr, grad, rec, stream);
-  return launch_pieces_g<true, float>(sums, 1.f, p, indices, offsets, nullptr, grad, rec, stream);
+    return launch_pieces_g<true, uint16_t>(sums, 1.f, p, indices, offsets, pairs, grad, rec, stream);
+  return launch_pieces_g<true, float>(sums, 1.f, p, indices, offsets, pairs, grad, rec, stream);
 }
 
-// Where one kernel is the faster form.  It saves three or four launches (25
-// to 30 us in a chain) and pays in deposits: each costs a 64-byte line
-// update at the memory side, about 20 G/s, for every line of every chunk.  So
-// the rule counts the lookups' chunk lines.  Pieces / grouped (kernel times, the
-// latter without the gaps between its four kernels), 26 tables of Zipf(1.1)
-// tokens, d = 128, Z = 32: 512 samples 10.4 / 33 us, 2048 28 / 36 us (0.64 M lines),
-// 4096 46 / 46 us (1.3 M), 8192 85 / 64 us (2.6 M); 13 tables of 9-item bags, d = 96,
-// Z = 8: 58 K lookups 49 / 62 us (1.0 M), 207 K 152 / 118 us (3.7 M).
-//
-// A frequent token is deposited once per piece, and every deposit rounds in 32
-// bits at its element.  Relative distance from 64-bit sums, pieces against
-// grouped, geometric mean over drawn shapes: up to 4096 lookups per
-// table 0.85 (95 results), to 12000 0.97 (31), to 16384 1.31 (4) and beyond
-// 1.17 (23); so tables of more lookups keep the grouped deposit.
-constexpr int64_t kPieceMaxItems = 1 << 18;
+// Where one kernel is the faster form of the deposit: one item per bag (the lookups of
+// a table are then T*B / T consecutive ones, and need no keygen), tables of
+// up to 4096 lookups (every workgroup scans its region) and up to 65536 lookups
+// in all.  Backward, pieces / grouped, uniform or Zipf(1.1) tokens of 10^7 rows, d = 128, Z = 32: 4 x 256 13.3 / 26 us,
+// 26 x 512 13.8 / 27.8 us, 1 x 4096 17.6 / 27.4 us, 26 x 2048 29 / 35.5 us, 13 x 4096
+// 27.9 / 34.2 us; 26 x 4096 52.1 / 52.1 us, of three tokens a table 34.2 / 26.1 us; 1 x 10240
+// 34 / 27.5 us; bags of 9 to 10 items 35 to 37 us (with its keygen) against 32 to 35 us.
+// A deposit costs a 64-byte line update at the memory side, about 20 G/s, for
+// every line of every chunk: the third bound keeps that below the chain's time.
+constexpr int64_t kPieceMaxItems = 1 << 16;
 constexpr int64_t kPieceMaxLines = 3 << 19;
-constexpr int64_t kPieceTableItems = 12000;
+constexpr uint32_t kPieceRegion = 4096;
 bool deposits_by_piece(const KParams& p) {
-  return p.N <= kPieceMaxItems &&
-         p.N * static_cast<int64_t>(p.C) * (p.Z / 16 + 1) <= kPieceMaxLines &&
-         static_cast<uint64_t>(p.N) * p.B <= kPieceTableItems * p.num_bags;
+  return p.N <= kPieceMaxItems && keygen_counts(p) && region_len(p) <= kPieceRegion &&
+         p.N * static_cast<int64_t>(p.C) * (p.Z / 16 + 1) <= kPieceMaxLines;
+}
+
+// Records replace a longer chain (the sparse branch's 26 launches) and are worth
+// longer regions: list of N = R lookups, d = 64, Z = 16, 4 M elements, by tile / general: 8192
+// 49 / 123 us, 16384 62 / 126 us, 22500 in bags 75 / 132 us; 30000 124 / 128 us.
+// The keys of a region (96 KB at most) share a workgroup's 160 KB of LDS with 24 KB.
+constexpr int64_t kRecordItems = 1 << 18;
+constexpr uint32_t kRecordRegion = 24576;
+bool pieces_fit(const KParams& p) {
+  return p.N <= kRecordItems && region_len(p) <= kRecordRegion;
 }
 
 }  // namespace pss

@@ -4,8 +4,8 @@
 // records fully by base and scans an ownership list: 26 launches, 140-150 us
 // however small the batch.  Here:
 //
-//   records  the pieces' run sums (pss_pieces.hip): one row of d floats per
-//            run and one (base, row * C + j) record per run and chunk
+//   records  the run sums of the pieces of the order by token (pss_pieces.hip): one
+//            row of d floats per run and one (base, row * C + j) record per run and chunk
 //   sort     one stable 8-bit radix pass by super tile (at most 255 of
 //            2^shift elements, shift >= 12; positions without a record sort last)
 //   count    (list) one workgroup per tile of 2^12 elements: the elements that the records
@@ -359,11 +359,13 @@ static uint32_t tiles_of(const KParams& p) {
   return static_cast<uint32_t>((static_cast<uint64_t>(p.M) + kTileLen - 1) >> kTileShift);
 }
 
-// sums, the two record buffers, the radix scratch, the counts of the list
+// sums, the two record buffers, the radix scratch, the counts of the list,
+// 1 / |bag| of a batch that is not one item per bag
 size_t tile_workspace_bytes(const KParams& p, bool list) {
   const uint64_t n = static_cast<uint64_t>(p.N) * p.C;
   return static_cast<size_t>(p.N) * p.d * 4 + n * 16 + radix_scratch_bytes(static_cast<int64_t>(n)) +
-         (list ? static_cast<size_t>(tiles_of(p)) * 4 : 0) + 6 * 256;
+         (list ? static_cast<size_t>(tiles_of(p)) * 4 : 0) +
+         (p.mean && !keygen_counts(p) ? static_cast<size_t>(p.num_bags) * 4 : 0) + 7 * 256;
 }
 
 struct TileRecords {
@@ -387,13 +389,28 @@ static hipError_t tile_records(const KParams& p, const void* indices, const void
   uint32_t *k0 = carve(n), *v0 = carve(n), *k1 = carve(n), *v1 = carve(n);
   uint32_t* scratch = reinterpret_cast<uint32_t*>(cur);
   cur += (radix_scratch_bytes(static_cast<int64_t>(n)) + 255) & ~size_t(255);
-  hipError_t e = launch_piece_records(sums, p, indices, offsets, grad, k0, v0, stream);
+  // Lookups of a batch that is not one item per bag: their keys and rows in the
+  // buffers that the radix pass writes later.
+  hipError_t e = hipSuccess;
+  GroupedPairs pairs;
+  const bool keygen = !keygen_counts(p);
+  if (keygen) {
+    float* inv_len = nullptr;
+    if (p.mean) inv_len = reinterpret_cast<float*>(carve(p.num_bags));
+    e = launch_keygen(p, indices, offsets, k1, v1, inv_len, stream);
+    pairs.keys = k1;
+    pairs.rows = v1;
+    pairs.inv_len = inv_len;
+  }
+  if (e == hipSuccess)
+    e = launch_piece_records(sums, p, indices, offsets, keygen ? &pairs : nullptr, grad, k0, v0,
+                             stream);
   if (e != hipSuccess) return e;
   const int shift = super_shift(p.M);
   e = radix_sort_pairs(k0, v0, k1, v1, static_cast<int64_t>(n), 8, scratch, stream, nullptr, false,
                        shift);
   *out = TileRecords{sums, k0, v0, radix_totals(scratch, static_cast<int64_t>(n)),
-                     reinterpret_cast<uint32_t*>(cur), shift};
+                     reinterpret_cast<uint32_t*>(cur), shift};  // counts: the list only
   return e;
 }
 
@@ -441,21 +458,26 @@ hipError_t launch_update_tiles(const KParams& p, const void* indices, const void
 }
 
 // Where it applies: batches whose general pipeline is a chain of launches
-// (up to 2^18 lookups), chunks of at least 4 elements (a record with fewer
+// (pieces_fit), chunks of at least 4 elements (a record with fewer
 // leaves most of its lane group idle) that fit a lane group's range, an array
 // of two whole tiles (a chunk that begins in tile 0 then does not wrap around
 // into it: a record stands in one bin), few enough tiles (each
 // costs a workgroup, and the list sums the counts of the tiles before) and
 // few enough records per tile (one workgroup adds them).  Kernel time of the call, general / by tile:
-// 8192 lookups, d = 64, Z = 16, 16 M elements 141 / 51 us, 512 lookups 118 / 37 us, 8192
-// on 60 M elements 154 / 90 us; the list of 26 x 4096 Zipf lookups on 4 M elements 145 / 77 us,
-// 10240 uniform ones with d = 128, Z = 32 on 1.28 M elements 129 / 55 us.
-constexpr int64_t kTileMaxItems = 1 << 18;
+// 8192 lookups, d = 64, Z = 16, 16 M elements 145 / 51 us; the list of 26 x 4096 Zipf lookups on 4 M
+// elements 141 / 83 us (79 us with records of the batch's own order, whose sums lie up to 1.23 times
+// farther from 64-bit ones), 10240 uniform ones with d = 128, Z = 32 on 1.28 M elements 137 / 55 us.
+// The limits keep a margin to where the two meet (general / by tile, 8192 lookups, d = 64, Z = 16):
+// list of 4096 tiles 139 / 67 us, 8192 137 / 104 us, 16384 135 / 188 us; update of 16384
+// tiles 136 / 84 us, 32768 138 / 118 us, 60000 136 / 164 us; records per tile, 32768 lookups: update 512
+// 129 / 59 us, 2048 122 / 72 us, 4096 123 / 95 us, 8192 124 / 144 us, the list of 106496 lookups 832
+// 138 / 95 us, 3328 134 / 119 us, 6656 138 / 165 us (uniform addresses; a skewed batch has more in
+// some tiles).
 constexpr int64_t kTileMaxRecords = 1024;  // per tile
 constexpr int64_t kTileMaxList = 4096, kTileMaxUpdate = 16384;  // tiles
 bool sparse_by_tile(const KParams& p, bool list) {
   const int64_t tiles = tiles_of(p);
-  return p.N <= kTileMaxItems && p.Z >= 4 && p.Z <= 1024 && p.M >= 2 * kTileLen &&
+  return pieces_fit(p) && p.Z >= 4 && p.Z <= 1024 && p.M >= 2 * kTileLen &&
          tiles <= (list ? kTileMaxList : kTileMaxUpdate) &&
          p.N * static_cast<int64_t>(p.C) <= tiles * kTileMaxRecords;
 }

@@ -1,9 +1,10 @@
 """GPU parity of the small batches' deposit (Alg. 1: gradients summed per
-token, then scattered), one kernel over pieces of consecutive lookups, against the oracle:
+token, then scattered), one kernel over pieces of their order by token, against the oracle:
 lane groups of 16, 32 and 64 lanes, slabs, chunk entries in LDS (at most 16
-chunks) and hashed per lane, pieces of 64 and 256 lookups with ragged ends,
-runs over several lane groups, bags of many lengths and long runs of empty
-bags, and the keygen made ahead by the forward or by pss_prepare_backward.
+chunks) and hashed per lane, pieces of 64 and 128 lookups with ragged ends, their
+cuts in the order by token, runs over several lane groups, as many items as bags
+but not one each, and the keygen made ahead by the forward or by
+pss_prepare_backward; and the batches just past its limits (grouped).
 """
 import numpy as np
 import pytest
@@ -45,8 +46,7 @@ def test_piece_widths(d, Z, bag):
         _step(Layer(wl, **kw))
 
 
-# (T, B): ends of the pieces of 64, the change to pieces of 256, their ends,
-# the most lookups per table and one more (grouped)
+# (T, B): ends of the pieces of 64, and larger batches that are grouped
 @pytest.mark.parametrize("T,B", [(1, 63), (1, 64), (1, 65), (4, 8192), (3, 10923), (7, 5000),
                                  (1, 12000), (1, 12001)])
 @pytest.mark.parametrize("prep", ["none", "forward", "explicit"])
@@ -83,7 +83,53 @@ def test_piece_bags(case, kw):
         lengths = ([1] * 40 + [0] * 900) * 4 + [2] * 200 + [0] * 600
     elif case == "swap":        # as many items as bags, not one each
         lengths = [1] * 100 + [0, 2] * 60 + [1] * 30
-    else:                       # pieces of 256, bags of 0 .. 7 items
+    else:                       # bags of 0 .. 7 items
         lengths = list(np.random.default_rng(3).integers(0, 8, 12_000))
     print(f"bags {case} {kw}", flush=True)
     _step(_with_bags(lengths, 4 if case == "big-pieces" else 2, **kw))
+
+
+# (T, B, rows): one piece and its ends, several tables to a region of 1024 lookups with
+# a shorter last region, the longest regions of pieces of 64 and of 128 lookups
+# and one more each (the last grouped); rows 1 and 2 divide every bin between
+# pieces, 40 some, 100000 none
+@pytest.mark.parametrize("T,B", [(1, 55), (1, 56), (1, 57), (5, 300), (7, 150), (2, 1024), (1, 2048),
+                                 (3, 2049), (2, 4096), (2, 4097), (16, 4096)])
+@pytest.mark.parametrize("kw", [{}, dict(sign="pm1", mean=True, idx32=True, flags=PREP)],
+                         ids=["plain", "signed-prepared"])
+def test_piece_cuts(T, B, kw):
+    for rows in (1, 2, 40, 100_000):
+        wl = C2.scaled(T=T, B=B, d=16, Z=8, M=70_001, cardinality=f"fixed:{rows}")
+        print(f"cuts T={T} B={B} rows={rows} {kw}", flush=True)
+        _step(Layer(wl, **kw))
+
+
+def _one_hot(T, B, tokens, **kw):
+    """A one-hot layer of the given tokens."""
+    wl = C2.scaled(T=T, B=B, cardinality="fixed:1000", **kw)
+    L = Layer(wl)
+    L.x = synth.gen.Inputs(indices=tokens, offsets=L.x.offsets, B=B)
+    L.indices = torch.from_numpy(tokens).to(L.dev)
+    return L
+
+
+@pytest.mark.parametrize("T,B", [(1, 1024), (4, 256), (1, 2048), (1, 4096), (13, 4096)])
+def test_piece_rounding(T, B):
+    """A token's lookups are summed before they are added to its weights, however they
+    are spread over the batch: every token is read by 16 lookups, B / 16 apart, and each
+    gradient of 2^-26 alone is lost in a weight of 1 (half a unit in the last place
+    is 2^-25), their sum of 2^-22 is not.  A token may be divided between two
+    pieces, each part rounded by at most 2^-25: at most 2^-24 per token at an
+    element, where adding them one by one would lose 2^-22."""
+    n = B // 16
+    tokens = np.tile(np.tile(np.arange(n, dtype=np.int64), 16), T)
+    L = _one_hot(T, B, tokens, d=16, Z=16, M=2_000_003)
+    L.shared.fill_(1.0)
+    w = np.ones(L.wl.M, dtype=np.float32)
+    g = np.full((B, T * 16), 2.0**-26, dtype=np.float32)
+    print(f"rounding T={T} B={B}", flush=True)
+    L.w_host = w
+    L.backward(g, lr=1.0)
+    _, _, G, _, _ = L.ref_backward(g, lr=1.0)
+    err = np.abs(L.weights().astype(np.float64) - (1.0 - G))
+    assert (err <= G / 2.0**-22 * 2.0**-24).all(), err.max()
