@@ -543,9 +543,9 @@ int plan_backward(void* shared, float* state, int64_t M, int32_t Z, int32_t d,
     return PSS_OK;
   }
   plan->g_bytes = plan->fused ? 0 : (static_cast<size_t>(M) * sizeof(float) + 255) & ~size_t(255);
-  plan->ws_bytes = variant != PSS_BWD_SORTED ? 0
-                   : plan->by_address       ? pss::addr_workspace_bytes(p)
-                                            : pss::sorted_workspace_bytes(p);
+  plan->ws_bytes = variant != PSS_BWD_SORTED || plan->by_piece ? 0
+                   : plan->by_address ? pss::addr_workspace_bytes(p)
+                                      : pss::sorted_workspace_bytes(p);
   return PSS_OK;
 }
 
@@ -751,8 +751,7 @@ int pss_backward_update(void* shared, float* state, int64_t M, int32_t Z, int32_
                                  plan.variant == PSS_BWD_SORTED &&
                                      (!plan.by_address || plan.runs) && !capturing(stream),
                                  &prep_lock);
-  // the grouping is already made, or needs no scratch
-  if (prep != nullptr || plan.by_piece) plan.ws_bytes = 0;
+  if (prep != nullptr) plan.ws_bytes = 0;  // the grouping is already made
   CallScratch scratch;
   const size_t need = plan.g_bytes + plan.runs_bytes + plan.ws_bytes;
   if (need > 0) {

@@ -77,3 +77,18 @@ def test_noalloc_rejects_more_than_its_scratch():
     assert st == pss.PSS_ERR_SCRATCH_LIMIT
     torch.cuda.synchronize()
     assert torch.equal(L.shared, w0)
+
+
+def test_noalloc_small_batch_needs_the_gradient_buffer_only():
+    """The one-kernel deposit of a small batch needs no grouping scratch: a float32
+    gradient buffer that fills the static array all but 4 KB is enough, as it is
+    for the allocating call."""
+    M = (pss.PSS_NOALLOC_SCRATCH_BYTES - 4096) // 4
+    wl = synth.get("c2").scaled(T=2, B=512, d=16, Z=4, M=M, cardinality="fixed:500",
+                                optimizer="adagrad")
+    print(f"noalloc small batch M={M}", flush=True)
+    L = Layer(wl, flags=pss.PSS_BWD_SORTED, s0=0.1)
+    grad = synth.make_grad(wl, 512)
+    _run(L, grad, noalloc=True)
+    w_ref, s_ref, G, A, _ = L.ref_backward(grad)
+    parity.check_update(L, L.weights(), L.state.cpu().numpy(), w_ref, s_ref, G, A, wl.lr)
