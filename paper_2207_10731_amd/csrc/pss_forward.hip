@@ -1,11 +1,12 @@
 // Forward of the PSS layer: hash -> chunk gather -> sum-pool (paper Sec. 2.4
 // forward(i) = (S e_i)^T M with the ROBE-Z mapping of Sec. 2.5).
 //
-// Three kernels, all bound by the memory system (rows written, chunks
+// Four kernels, all bound by the memory system (rows written, chunks
 // gathered):
 //   rows   one item per bag (as many items as bags): a wavefront takes a run
 //          of consecutive bags of a table, a lane group holds one row;
 //   bags   any other batch: a lane group pools one bag;
+//   long   few long bags: a workgroup pools one bag;
 //   tiled  one item per bag, at least 2^20 bags and an array beyond the
 //          aggregate L2: a wavefront takes 64 bags, sorts their tokens and
 //          gathers each distinct one once.
@@ -353,6 +354,97 @@ __global__ __launch_bounds__(kBlockThreads, 8) void forward_bags_kernel(
                 acc, p.rows_bf16);
 }
 
+// Items [e0, e1) of a bag pooled by one lane group, AHEAD of them in flight,
+// without the table.
+template <typename WT, int V, int AHEAD, bool SIGN>
+__device__ __forceinline__ typename Piece<V>::type pool_items(
+    const WT* __restrict__ w, const KParams& p, const void* __restrict__ indices, const int64_t e0,
+    const int64_t e1, const uint32_t t, const uint32_t kk, const uint32_t jc, const KeygenOut& kg,
+    const bool keys, const uint32_t row) {
+  typename Piece<V>::type acc = {};
+#pragma unroll 1
+  for (int64_t e = e0; e < e1; e += AHEAD) {
+    uint32_t en[AHEAD];
+    bool split = false;
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q)  // past the end: the last one again
+      en[q] = index_at(indices, static_cast<uint64_t>(e + q < e1 ? e + q : e1 - 1), p.idx32);
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q) {
+      const uint32_t h = item_hash(en[q], t * p.C, p.TC, p.a, p.b);
+      if (keys && e + q < e1) {
+        kg.keys[e + q] = h;
+        kg.rows[e + q] = row;
+      }
+      en[q] = item_entry<SIGN>(p, h, jc);
+      split |= splits<V, SIGN>(en[q], kk, p.M);
+    }
+    if (__ballot(split)) {
+#pragma unroll 1
+      for (int q = 0; q < AHEAD; ++q) {
+        uint32_t ent = en[0];
+#pragma unroll
+        for (int r = 1; r < AHEAD; ++r) ent = r == q ? en[r] : ent;
+        if (e + q < e1) acc += sign_piece<SIGN>(gather_split<WT, V, SIGN>(w, ent, kk, p.M), ent);
+      }
+    } else {
+      typename Piece<V>::type v[AHEAD];
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q) v[q] = gather<WT, V, SIGN>(w, en[q], kk, p.M);
+#pragma unroll
+      for (int q = 0; q < AHEAD; ++q)
+        if (e + q < e1) acc += sign_piece<SIGN>(v[q], en[q]);
+    }
+  }
+  return acc;
+}
+
+__device__ __forceinline__ float shfl_xor_piece(float x, int m) { return __shfl_xor(x, m); }
+__device__ __forceinline__ f32x4 shfl_xor_piece(f32x4 x, int m) {
+  return f32x4{__shfl_xor(x.x, m), __shfl_xor(x.y, m), __shfl_xor(x.z, m), __shfl_xor(x.w, m)};
+}
+
+// Few long bags: a workgroup per bag (blockIdx.x; slab blockIdx.y), a share of its
+// items to every lane group of its wavefronts.  One lane group per bag would be
+// bound by its chain of index, hash and gather: a bag of 50000 items, d = 16 (Z = 4) 15.7 ms / 288 us
+// (one lane group / this kernel), d = 128 (Z = 32) 7.4 / 1.2 ms; 64 bags of 400 items, d = 64
+// 76 / 9.6 us.
+template <typename WT, int V, int LPB, bool SIGN>
+__global__ __launch_bounds__(kBlockThreads) void forward_long_kernel(
+    const WT* __restrict__ w, const KParams p, const void* __restrict__ indices,
+    const void* __restrict__ offsets, void* __restrict__ out, const KeygenOut kg) {
+  constexpr int GP = kWave / LPB, kShares = kWavesPerBlock * GP;
+  __shared__ __align__(16) float part[kWavesPerBlock][LPB * V];
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
+  const int grp = wv * GP + lane / LPB, gl = lane % LPB;
+  const uint32_t g = blockIdx.x, t = g / p.B, b = g - t * p.B, row = b * p.T + t;
+  const RowLane<V, LPB> rl(p, gl);
+  const bool keys = kg.keys != nullptr && blockIdx.y == 0;
+  int64_t e0 = offset_at(offsets, g, p.idx32);
+  int64_t e1 = offset_at(offsets, static_cast<uint64_t>(g) + 1, p.idx32);
+  e0 = e0 < 0 ? 0 : (e0 > p.N ? p.N : e0);
+  e1 = e1 < 0 ? 0 : (e1 > p.N ? p.N : e1);
+  if (e1 < e0) e1 = e0;
+  const int64_t share = (e1 - e0 + kShares - 1) / kShares;
+  const int64_t i0 = e0 + grp * share, i1 = i0 + share < e1 ? i0 + share : e1;
+  typename Piece<V>::type sum = pool_items<WT, V, 8, SIGN>(w, p, indices, i0, i1, t, rl.kk, rl.jc, kg,
+                                                           keys && gl == 0, row);
+#pragma unroll
+  for (int off = LPB; off < kWave; off <<= 1) sum += shfl_xor_piece(sum, off);
+  if (lane < LPB) *reinterpret_cast<typename Piece<V>::type*>(&part[wv][gl * V]) = sum;
+  __syncthreads();
+  const float n = static_cast<float>(e1 - e0);
+  if (keys && p.mean && threadIdx.x == 0 && e1 > e0) kg.inv_len[row] = 1.f / n;
+  if (threadIdx.x >= LPB || !rl.act) return;
+  sum = typename Piece<V>::type{};
+#pragma unroll
+  for (int v = 0; v < kWavesPerBlock; ++v)
+    sum += *reinterpret_cast<const typename Piece<V>::type*>(&part[v][gl * V]);
+  if (p.mean && e1 > e0) sum /= n;
+  store_piece(out, static_cast<uint64_t>(b) * p.row_stride + static_cast<uint64_t>(t) * p.d + rl.c, sum,
+              p.rows_bf16);
+}
+
 // As many items as bags (N == T*B), usually one per bag: a wavefront takes NB = U * GP
 // consecutive bags, a lane each for the index and item hash, then gathers and stores U
 // pieces per lane.  A wavefront that meets a bag of another length or position, or a
@@ -677,12 +769,29 @@ static hipError_t launch_tiled(const WT* w, const KParams& p, const void* indice
   return launch_tiled_t<WT, 8, 2, SIGN>(w, p, indices, offsets, out, stream, touch);
 }
 
+// Bags of 64 items or more on average, too few of them to fill the chip by lane groups (a
+// wavefront of the bags kernel on every SIMD) or by workgroups.  Bags / long kernel, d = 16, Z = 4, 64
+// items each: 64 bags 24.6 / 5.4 us, 4000 30 / 24 us, 8000 31 / 43 us; d = 128, Z = 32: 1000 bags
+// 15.2 / 7.4 us, 2000 (1000 wavefronts) 16.3 / 10.3 us; from there on the bags kernel is bound by
+// its gathers.
+constexpr uint64_t kLongBagItems = 64, kLongBagWaves = 1024, kLongBagBlocks = 4096;
+static bool few_long_bags(const KParams& p, uint64_t waves, uint32_t slabs) {
+  return !one_per_bag(p) && waves < kLongBagWaves && p.num_bags * slabs <= kLongBagBlocks &&
+         static_cast<uint64_t>(p.N) >= kLongBagItems * p.num_bags;
+}
+
 template <typename WT, int V, int LPB, bool SIGN>
 static hipError_t launch_rows_t(const WT* w, const KParams& p, const void* indices,
                                 const void* offsets, void* out, hipStream_t stream,
                                const Touch& touch, const KeygenOut& kg) {
   const uint64_t per_wave = (kWave / LPB) * (one_per_bag(p) ? kRowBatch : 1);
   const uint32_t slabs = (p.d + LPB * V - 1) / (LPB * V);
+  if (few_long_bags(p, p.num_bags / per_wave * slabs, slabs)) {
+    hipLaunchKernelGGL((forward_long_kernel<WT, V, LPB, SIGN>),
+                       dim3(static_cast<uint32_t>(p.num_bags), slabs), dim3(kBlockThreads), 0, stream, w,
+                       p, indices, offsets, out, kg);
+    return hipGetLastError();
+  }
   return launch_shares((p.num_bags + per_wave - 1) / per_wave, touch,
                        [&](uint32_t blocks, uint64_t wave0, const Touch& t) {
     if (one_per_bag(p))

@@ -123,3 +123,54 @@ def test_more_rows_than_one_grid():
         assert (part == want).all()
     del out
     torch.cuda.empty_cache()
+
+
+# Few long bags, pooled by a workgroup each: lane groups of 4 to 64 lanes, one and
+# four elements per lane, slabs, chunks wrapping past the end of a small array,
+# empty bags and bags shorter than a workgroup's shares among long ones; then the
+# backward of a prepared batch, whose keys the same kernel writes.
+@pytest.mark.parametrize("d,Z", [(4, 1), (7, 7), (16, 4), (40, 8), (50, 5), (64, 16), (128, 32),
+                                 (200, 50), (600, 24)])
+@pytest.mark.parametrize("kw", [{}, dict(sign="sparse", mean=True, idx32=True, rows_bf16=True),
+                                dict(sign="pm1", mean=True, flags=pss.PSS_PREPARE_BACKWARD)],
+                         ids=["plain", "options", "prepared"])
+def test_few_long_bags(d, Z, kw):
+    lengths = np.array([700, 0, 1, 3, 64, 65, 2000, 31, 0, 9, 256, 1111])
+    for wd in ("f32", "bf16"):
+        wl = C2.scaled(T=2, B=6, d=d, Z=Z, M=max(2 * d, 900) + 1, cardinality="fixed:500",
+                       weight_dtype=wd)
+        print(f"long bags d={d} Z={Z} {wd} {kw}", flush=True)
+        L = Layer(wl, **kw)
+        offsets = np.zeros(13, dtype=np.int64)
+        np.cumsum(lengths, out=offsets[1:])
+        idx = np.random.default_rng(8).integers(0, 500, int(offsets[-1]), dtype=np.int64)
+        L.x = synth.gen.Inputs(indices=idx, offsets=offsets, B=L.B)
+        L.indices = torch.from_numpy(idx).to(L.dev).to(L.indices.dtype)
+        L.offsets = torch.from_numpy(offsets).to(L.dev).to(L.offsets.dtype)
+        L.hp.num_indices = len(idx)
+        got = L.forward()
+        ref, s_abs = L.ref_forward()
+        parity.check_forward(got, ref, s_abs, 1e-5, rows_bf16=L.rows_bf16)
+        if "flags" in kw:
+            g = synth.make_grad(wl, B=6)
+            L.backward(g)
+            w_ref, s_ref, G, A, _ = L.ref_backward(g)
+            parity.check_update(L, L.weights(), None, w_ref, s_ref, G, A, wl.lr)
+
+
+# Ends of its range: 64 items a bag on average and just fewer, 4096 bags and one more.
+@pytest.mark.parametrize("B,extra", [(64, 0), (64, -1), (4096, 0), (4097, 0)])
+def test_long_bag_limits(B, extra):
+    wl = C2.scaled(T=1, B=B, d=16, Z=4, M=5000, cardinality="fixed:3000", bag="poisson:64:64:64")
+    print(f"long bag limits B={B} extra={extra}", flush=True)
+    L = Layer(wl)
+    assert L.x.N == 64 * B
+    if extra:
+        L.x.offsets[-1] += extra
+        L.x = synth.gen.Inputs(indices=L.x.indices[:extra], offsets=L.x.offsets, B=B)
+        L.indices = torch.from_numpy(L.x.indices).to(L.dev)
+        L.offsets = torch.from_numpy(L.x.offsets).to(L.dev)
+        L.hp.num_indices = L.x.N
+    got = L.forward()
+    ref, s_abs = L.ref_forward()
+    parity.check_forward(got, ref, s_abs, 1e-5)
