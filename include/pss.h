@@ -338,6 +338,22 @@ int pss_debug_signs(int64_t M, int32_t Z, int32_t d, const pss_hash_params* hash
  * capture, not for concurrent callers. */
 int pss_debug_reduce_events(void* before, void* after);
 
+/* Which form of its kernels a backward call of these arguments takes (with
+ * `list` != 0: a pss_gradient_sparse call), for tests that have to reach one.
+ * adagrad: whether the call passes a state.  Host only. */
+enum {
+  PSS_ROUTE_NONE = 0,    /* no lookups */
+  PSS_ROUTE_ATOMIC = 1,
+  PSS_ROUTE_GROUPED = 2, /* SORTED: radix sort by token, then the reduce kernel */
+  PSS_ROUTE_PIECES = 3,  /* SORTED: one kernel */
+  PSS_ROUTE_ADDRESS = 4, /* SORTED by address, a record per (lookup, dim) */
+  PSS_ROUTE_RUNS = 5,    /* ... per run sum and chunk */
+  PSS_ROUTE_SPARSE = 6,
+  PSS_ROUTE_TILES = 7    /* SPARSE by array tile */
+};
+int pss_debug_backward_route(int64_t M, int32_t Z, int32_t d, const pss_hash_params* hash_params,
+                             int32_t adagrad, int32_t list, int32_t* route);
+
 /* Host evaluation of the same hash code the kernels run (no GPU needed):
  * base_out[e*C + j] = h(indices[e], t(e), j) for host arrays indices[N],
  * offsets[T*B+1] (int64 whatever the flags say) and base_out[N*C].  Returns

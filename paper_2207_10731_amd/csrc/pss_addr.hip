@@ -254,15 +254,6 @@ constexpr int kRunsBatch = 8;  // records whose payload pieces are requested tog
 constexpr int kRunsOpt = 4;    // elements per lane updated together
 constexpr uint32_t kRunsStage = 1024;  // records staged in LDS at a time
 
-// Whether the chunk of Z elements from `base` (wrapping past M) has an
-// element in [x0, x0 + len).
-__device__ __forceinline__ bool chunk_reaches(uint32_t base, uint32_t Z, uint32_t M, uint32_t x0,
-                                              uint32_t len) {
-  const uint64_t last = static_cast<uint64_t>(base) + Z - 1;
-  if (last < M) return base < x0 + len && last >= x0;
-  return base < x0 + len || x0 <= last - M;  // [base, M) and [0, last - M]
-}
-
 // One workgroup per tile of the array, each of its wavefronts owning a
 // range of kRunsRange consecutive elements of the tile in LDS.  Records are
 // (base, slot): the chunk covers elements (base + k) mod M, k < Z, with

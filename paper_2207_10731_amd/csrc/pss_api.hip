@@ -842,6 +842,33 @@ int pss_debug_signs(int64_t M, int32_t Z, int32_t d, const pss_hash_params* hash
   return hip_status(pss::launch_debug_addresses(p, indices, offsets, nullptr, sign_out, stream));
 }
 
+int pss_debug_backward_route(int64_t M, int32_t Z, int32_t d, const pss_hash_params* hash_params,
+                             int32_t adagrad, int32_t list, int32_t* route) {
+  if (route == nullptr) return PSS_ERR_INVALID_ARG;
+  *route = PSS_ROUTE_NONE;
+  if (list) {
+    const int st = check_common(M, Z, d, hash_params);
+    if (st != PSS_OK) return st;
+    const KParams p = make_params(M, Z, d, hash_params);
+    if (p.N > 0) *route = pss::sparse_by_tile(p, true) ? PSS_ROUTE_TILES : PSS_ROUTE_SPARSE;
+    return PSS_OK;
+  }
+  float some[1];  // for the plan's null checks: no pointer is followed
+  BackwardPlan plan;
+  const int st = plan_backward(some, adagrad ? some : nullptr, M, Z, d, hash_params, some, some, some,
+                               0.f, &plan);
+  if (st == kNothingToDo) return PSS_OK;
+  if (st != PSS_OK) return st;
+  *route = plan.variant == PSS_BWD_ATOMIC   ? PSS_ROUTE_ATOMIC
+           : plan.variant == PSS_BWD_SPARSE ? (pss::sparse_by_tile(plan.p, false) ? PSS_ROUTE_TILES
+                                                                                  : PSS_ROUTE_SPARSE)
+           : plan.runs                      ? PSS_ROUTE_RUNS
+           : plan.by_address                ? PSS_ROUTE_ADDRESS
+           : plan.by_piece                  ? PSS_ROUTE_PIECES
+                                            : PSS_ROUTE_GROUPED;
+  return PSS_OK;
+}
+
 int pss_debug_reduce_events(void* before, void* after) {
   if ((before == nullptr) != (after == nullptr)) return PSS_ERR_INVALID_ARG;
   pss::set_reduce_events(static_cast<hipEvent_t>(before), static_cast<hipEvent_t>(after));

@@ -319,4 +319,16 @@ __device__ __forceinline__ int bag_of_item(const Tile& tl, int64_t e) {
   return lo;
 }
 
+// A record without a chunk (no run begins at its position, or the chunk is not read).
+constexpr uint32_t kNoChunk = 0xffffffffu;
+
+// Whether the chunk of Z elements from `base` (wrapping past M) has an
+// element in [x0, x0 + len).
+__device__ __forceinline__ bool chunk_reaches(uint32_t base, uint32_t Z, uint32_t M, uint32_t x0,
+                                              uint32_t len) {
+  const uint64_t last = static_cast<uint64_t>(base) + Z - 1;
+  if (last < M) return base < x0 + len && last >= x0;
+  return base < x0 + len || x0 <= last - M;  // [base, M) and [0, last - M]
+}
+
 }  // namespace pss

@@ -277,7 +277,6 @@ __device__ __forceinline__ int token_order(const KParams& p, const void* __restr
 // position and chunk j a record (rec_keys, rec_ids): the chunk's base and
 // (p0 + q) * C + j, or kNoChunk where no run begins or the chunk is not read.
 // Every sum is then taken in a fixed order.
-constexpr uint32_t kNoChunk = 0xffffffffu;
 template <int EPL, int LPB, int P, bool SIGN, bool I32, bool REC, typename GT>
 __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
     float* __restrict__ dst, const float scale, const KParams p, const void* __restrict__ indices,

@@ -31,7 +31,6 @@ constexpr int kTileShift = 12;
 constexpr uint32_t kTileLen = 1u << kTileShift;
 constexpr int kTileThreads = 256;
 constexpr int kTileStage = 4;  // records per thread staged together
-constexpr uint32_t kNoChunk = 0xffffffffu;
 constexpr uint32_t kTileWords = kTileLen / 32;  // bits of the touched elements
 constexpr int kTileBatch = 8;                   // records a lane group requests together
 
@@ -41,15 +40,6 @@ static int super_shift(uint32_t M) {
   int s = kTileShift;
   while (((M - 1) >> s) > 254) ++s;
   return s;
-}
-
-// Whether the chunk of Z elements from `base` (wrapping past M) has an
-// element in [x0, x0 + len).
-__device__ __forceinline__ bool reaches(uint32_t base, uint32_t Z, uint32_t M, uint32_t x0,
-                                        uint32_t len) {
-  const uint64_t last = static_cast<uint64_t>(base) + Z - 1;
-  if (last < M) return base < x0 + len && last >= x0;
-  return base < x0 + len || x0 <= last - M;  // [base, M) and [0, last - M]
 }
 
 // starts[u] = first of the sorted records of super tile u (starts[256]: their
@@ -133,7 +123,7 @@ __global__ __launch_bounds__(kTileThreads) void tile_count_kernel(
         uint32_t bv = base[0];
 #pragma unroll
         for (int q = 1; q < kTileStage; ++q) bv = q == v ? base[q] : bv;
-        if (bv != kNoChunk && reaches(bv, Z, M, x0, len)) touch_bits(bits, bv, x0, len, M, Z);
+        if (bv != kNoChunk && chunk_reaches(bv, Z, M, x0, len)) touch_bits(bits, bv, x0, len, M, Z);
       }
     }
   });
@@ -200,7 +190,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void tile_apply_kernel(
         base[v] = r < hi ? keys[r] : kNoChunk;
         id[v] = r < hi ? ids[r] : 0u;
         bin[v] = -1;
-        if (base[v] != kNoChunk && reaches(base[v], Z, M, x0, len)) {
+        if (base[v] != kNoChunk && chunk_reaches(base[v], Z, M, x0, len)) {
           const uint32_t o = base[v] - x0;  // below len: begins in the tile
           bin[v] = o < len ? static_cast<int>(o / kRange) + 1 : 0;
         }

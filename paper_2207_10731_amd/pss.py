@@ -30,6 +30,8 @@ PSS_SIGN_PM1, PSS_SIGN_SPARSE, PSS_SIGN_MASK = 1 << 2, 2 << 2, 3 << 2
 PSS_POOL_MEAN, PSS_INDEX_I32, PSS_ROWS_BF16 = 1 << 4, 1 << 5, 1 << 6
 PSS_PREPARE_BACKWARD = 1 << 7
 PSS_DEPOSIT_BY_ADDRESS = 1 << 8
+(PSS_ROUTE_NONE, PSS_ROUTE_ATOMIC, PSS_ROUTE_GROUPED, PSS_ROUTE_PIECES, PSS_ROUTE_ADDRESS,
+ PSS_ROUTE_RUNS, PSS_ROUTE_SPARSE, PSS_ROUTE_TILES) = range(8)
 
 
 class PssError(RuntimeError):
@@ -81,12 +83,13 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.pss_status_string.restype = ctypes.c_char_p
     lib.pss_release_scratch.argtypes = []
     lib.pss_debug_reduce_events.argtypes = [vp, vp]
+    lib.pss_debug_backward_route.argtypes = [i64, i32, i32, hp, i32, i32, vp]
     for name in ("pss_hash_params_from_seed", "pss_forward", "pss_backward_update",
                  "pss_backward_update_noalloc",
                  "pss_prepare_backward", "pss_debug_addresses", "pss_debug_signs",
                  "pss_gradient_sparse",
                  "pss_hash_bases_host", "pss_hash_signs_host", "pss_validate_offsets_host",
-                 "pss_release_scratch", "pss_debug_reduce_events"):
+                 "pss_release_scratch", "pss_debug_reduce_events", "pss_debug_backward_route"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     # Return the library's runtime objects (kept scratch, prepared-grouping
@@ -437,6 +440,16 @@ def pss_validate_offsets_host(offsets, num_bags, N) -> int:
         return PSS_ERR_INVALID_ARG
     return load_library().pss_validate_offsets_host(off.ctypes.data_as(ctypes.c_void_p),
                                                     num_bags, N)
+
+
+def pss_debug_backward_route(M, Z, d, hash_params, adagrad=False, sparse_list=False):
+    """The PSS_ROUTE_* of a backward call of these arguments (with sparse_list:
+    of pss_gradient_sparse); host only."""
+    route = ctypes.c_int32()
+    _check(load_library().pss_debug_backward_route(M, Z, d, ctypes.byref(hash_params), int(adagrad),
+                                                   int(sparse_list), ctypes.byref(route)),
+           "pss_debug_backward_route")
+    return route.value
 
 
 def pss_debug_reduce_events(before=None, after=None):

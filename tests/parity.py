@@ -96,6 +96,12 @@ class Layer:
             return self.shared.view(torch.int16).cpu().numpy().view(np.uint16)
         return self.shared.cpu().numpy()
 
+    def route(self, sparse_list=False):
+        """The PSS_ROUTE_* that a backward (or the sparse gradient) takes."""
+        wl = self.wl
+        return pss.pss_debug_backward_route(wl.M, wl.Z, wl.d, self.hp, self.state is not None,
+                                            sparse_list)
+
     def debug_signs(self):
         wl = self.wl
         out = torch.empty((self.x.N, wl.C), dtype=torch.int8, device=self.dev)

@@ -101,7 +101,9 @@ def test_piece_cuts(T, B, kw):
     for rows in (1, 2, 40, 100_000):
         wl = C2.scaled(T=T, B=B, d=16, Z=8, M=70_001, cardinality=f"fixed:{rows}")
         print(f"cuts T={T} B={B} rows={rows} {kw}", flush=True)
-        _step(Layer(wl, **kw))
+        L = Layer(wl, **kw)
+        assert L.route() == (pss.PSS_ROUTE_GROUPED if B > 4096 else pss.PSS_ROUTE_PIECES)
+        _step(L)
 
 
 def _one_hot(T, B, tokens, **kw):
@@ -124,6 +126,7 @@ def test_piece_rounding(T, B):
     n = B // 16
     tokens = np.tile(np.tile(np.arange(n, dtype=np.int64), 16), T)
     L = _one_hot(T, B, tokens, d=16, Z=16, M=2_000_003)
+    assert L.route() == pss.PSS_ROUTE_PIECES
     L.shared.fill_(1.0)
     w = np.ones(L.wl.M, dtype=np.float32)
     g = np.full((B, T * 16), 2.0**-26, dtype=np.float32)
@@ -133,3 +136,36 @@ def test_piece_rounding(T, B):
     _, _, G, _, _ = L.ref_backward(g, lr=1.0)
     err = np.abs(L.weights().astype(np.float64) - (1.0 - G))
     assert (err <= G / 2.0**-22 * 2.0**-24).all(), err.max()
+
+
+# The grouped deposit (radix sort, then the reduce kernel, which large batches take):
+# widths of one to two slabs, more chunks than the LDS table holds (d / Z > 16),
+# the options, and the keygen made ahead.
+@pytest.mark.parametrize("d,Z", [(16, 4), (64, 16), (64, 2), (128, 32), (256, 64), (512, 128), (260, 52)])
+@pytest.mark.parametrize("kw", [dict(sign="pm1"), dict(sign="sparse", mean=True, idx32=True),
+                                dict(rows_bf16=True, mean=True), dict(idx32=True, flags=PREP),
+                                dict(sign="sparse", rows_bf16=True, flags=PREP)],
+                         ids=["pm1", "sparse-mean-i32", "bf16rows-mean", "i32-prep", "sparse-bf16rows-prep"])
+def test_grouped_options(d, Z, kw):
+    for B, card, bag in ((4500, "fixed:700", "one"), (1300, "fixed:40000", "poisson:4:0:30")):
+        wl = C2.scaled(T=1, B=B, d=d, Z=Z, M=50_000, cardinality=card, bag=bag, optimizer="adagrad")
+        print(f"grouped d={d} Z={Z} B={B} {bag} {kw}", flush=True)
+        L = Layer(wl, s0=0.1, **kw)
+        assert L.route() == pss.PSS_ROUTE_GROUPED
+        _step(L)
+
+
+@pytest.mark.parametrize("kw", [dict(mean=True), dict(mean=True, flags=PREP),
+                                dict(sign="pm1", mean=True, idx32=True, flags=PREP)],
+                         ids=["plain", "prepared", "signed-i32-prepared"])
+@pytest.mark.parametrize("T,B", [(1, 4608), (2, 150_000)])
+def test_grouped_irregular_one_hot(T, B, kw):
+    """As many items as bags, not one each: the keygen's bag search."""
+    lengths = np.ones(T * B, dtype=np.int64)
+    at = np.random.default_rng(6).permutation(T * B)[:T * B // 8]
+    lengths[at[::2]], lengths[at[1::2]] = 0, 2
+    lengths[0] += T * B - lengths.sum()
+    print(f"grouped irregular T={T} B={B} {kw}", flush=True)
+    L = _with_bags(lengths, T, **kw)
+    assert L.route() == pss.PSS_ROUTE_GROUPED
+    _step(L)

@@ -64,8 +64,8 @@ def test_tiles(d, Z, M):
 
 
 @pytest.mark.parametrize("T,B,M", [
-    (2, 16384, 40_000),    # 3 tokens per table: hundreds of records of one chunk
-    (1, 1 << 18, 5_000_000),      # the largest batch
+    (2, 16384, 40_000),           # more records than the tiles take (general)
+    (1, 1 << 18, 5_000_000),      # one table of more lookups than a region (general)
     (1, (1 << 18) + 1, 5_000_000),
     (4, 4096, 4096 * 4096),       # the most tiles of a list
     (4, 4096, 4096 * 4096 + 1),
@@ -87,3 +87,47 @@ def test_tile_overlaps(d, Z):
                    optimizer="adagrad")
     print(f"tile overlaps d={d} Z={Z}", flush=True)
     _check(wl)
+
+
+# 3 tokens per table: thousands of records of a chunk in one bin, over several stages
+@pytest.mark.parametrize("T,B,d,Z", [(2, 16384, 16, 16), (1, 8000, 64, 32), (1, 4096, 128, 128)])
+def test_tile_skew(T, B, d, Z):
+    wl = C2.scaled(T=T, B=B, d=d, Z=Z, M=33 * 4096 + 5, cardinality="fixed:3", optimizer="adagrad")
+    print(f"tile skew T={T} B={B} d={d} Z={Z}", flush=True)
+    L = Layer(wl, flags=pss.PSS_BWD_SPARSE)
+    assert L.route() == pss.PSS_ROUTE_TILES and L.route(True) == pss.PSS_ROUTE_TILES
+    _check(wl)
+
+
+# The rule's limits: 1024 records per tile on average, 2^18 lookups, a table of 24576
+# lookups (or as many in a batch of several items per bag)
+@pytest.mark.parametrize("T,B,d,Z,M,bag,tiled", [
+    (1, 10 * 1024, 16, 16, 10 * 4096, "one", True),
+    (1, 10 * 1024 + 1, 16, 16, 10 * 4096, "one", False),
+    (64, 4096, 8, 8, 300 * 4096, "one", True),
+    (64, 4097, 8, 8, 300 * 4096, "one", False),
+    (1, 24576, 16, 16, 200_000, "one", True),
+    (1, 24577, 16, 16, 200_000, "one", False),
+    (2, 6144, 16, 16, 200_000, "poisson:2:2:2", True),
+    (2, 6145, 16, 16, 200_000, "poisson:2:2:2", False),
+])
+def test_tile_rule(T, B, d, Z, M, bag, tiled):
+    wl = C2.scaled(T=T, B=B, d=d, Z=Z, M=M, cardinality="fixed:5000", bag=bag)
+    print(f"tile rule T={T} B={B} M={M} {bag}", flush=True)
+    L = Layer(wl, flags=pss.PSS_BWD_SPARSE)
+    want = pss.PSS_ROUTE_TILES if tiled else pss.PSS_ROUTE_SPARSE
+    assert L.route() == want and L.route(True) == want
+    _check(wl)
+
+
+@pytest.mark.parametrize("tiles,tiled", [(16384, True), (16385, False)])
+def test_tile_update_most_tiles(tiles, tiled):
+    """The most tiles of an update, and one more (general)."""
+    wl = C2.scaled(T=1, B=500, d=16, Z=16, M=4096 * tiles, cardinality="fixed:9000")
+    print(f"tile update tiles={tiles}", flush=True)
+    L = Layer(wl, flags=pss.PSS_BWD_SPARSE)
+    assert L.route() == (pss.PSS_ROUTE_TILES if tiled else pss.PSS_ROUTE_SPARSE)
+    g = synth.make_grad(wl, B=L.B)
+    L.backward(g)
+    w_ref, s_ref, G, A, _ = L.ref_backward(g)
+    parity.check_update(L, L.weights(), None, w_ref, s_ref, G, A, wl.lr)
