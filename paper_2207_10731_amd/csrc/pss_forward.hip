@@ -72,7 +72,13 @@ __device__ __forceinline__ int64_t offset_at(const void* off, uint64_t g, uint32
 //         of its lines would otherwise be fetched by a random read (128 MB
 //         array, 26 x 262144 rows of 256 bytes: 970 -> 751 us, the training step
 //         2156 -> 1932 us).  Where it has not (the same step over and over, nothing
-//         else running), the pass costs 17 to 28 us of 1860.
+//         else running), the pass costs 17 to 28 us of 1860.  Rows of 256 bytes, forward
+//         without / with the pass, array evicted and still cached: 128 MB gathered
+//         twice 194 / 166 and 115 / 132 us, 4 times 358 / 286 and 231 / 246 us, 8 times
+//         580 / 502 and 439 / 455 us, 16 times 1011 / 939 and 862 / 874 us: from 8 times on what
+//         it may cost is below 4%.  192 MB, 8 times 882 / 780 and 690 / 719 us; a 256 MB array
+//         does not stay cached either way (1174 / 1037 and 1116 / 953 us) and is left to its
+//         gathers: beside other data the pass would evict its own lines.
 struct Touch {
   uint32_t index = 0;
   uint64_t bytes = 0;
