@@ -214,10 +214,12 @@ def test_prepared_on_two_streams():
 
 
 
-# The streamed forward (one item per bag, d in {64, 128, 256}, Z % 4 == 0,
-# array within the aggregate L2) writes the keygen stage of the grouping; the
-# backward finishes it.  Shapes: the XCD groups' share of the sort tiles,
-# ragged last tiles, a grid too small for the XCD groups.
+# Batches with as many items as bags: the forward call makes the keygen on the
+# caller's stream, by the forward kernel itself where the backward is one kernel
+# that takes the keys as they are (route PIECES), else by a kernel ahead of it,
+# whose grouping the backward finishes (route GROUPED: c2-4000).  Shapes: the XCD
+# groups' share of the sort tiles, ragged last tiles, a grid too small for the
+# XCD groups.
 FUSED = {
     "c2-700": dict(key="c2", B=700),
     "c2-4000": dict(key="c2", B=4000),        # 51 sort tiles over 8 XCD groups
@@ -250,7 +252,7 @@ def test_fused_keygen_step(case, opt):
 
 def _irregular(T, B, seed, k, n_index=50_000):
     """N == T*B items, but k empty bags and k bags of two items: the
-    streamed forward's slow path, and the keygen's bag search."""
+    one-row-per-bag forward's slow path, and the keygen's bag search."""
     rng = np.random.default_rng(seed)
     pick = rng.permutation(T * B)
     lengths = np.ones(T * B, dtype=np.int64)
@@ -264,8 +266,8 @@ def _irregular(T, B, seed, k, n_index=50_000):
 
 @pytest.mark.parametrize("mean", [False, True])
 def test_fused_keygen_irregular_bags(mean):
-    """As many items as bags but not one per bag: the forward still streams
-    and writes the keygen stage, whose items search their bags."""
+    """As many items as bags but not one per bag: the forward kernel still
+    writes the keys, bag by bag."""
     wl = synth.get("c2").scaled(T=6, M=700_000)
     L = Layer(wl, B=900, flags=pss.PSS_BWD_SORTED | PREP, mean=mean)
     indices, offsets = _irregular(wl.T, L.B, 5, 300)
