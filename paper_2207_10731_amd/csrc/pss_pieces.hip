@@ -19,9 +19,9 @@
 // Pieces of the batch's own order, each token deposited once per piece that holds
 // it, need no order stage, but every deposit rounds in 32 bits at its element: the
 // distance from 64-bit sums grew up to 1.5 times (2 tables of 3927
-// Zipf lookups, d = 256, Z = 8).  In the order by token it is 0.63 to 1.02 times
-// the grouped deposit's, shape by shape (a single token alone, whose distance differs
-// 0.8 to 1.8 times between two runs, apart).
+// Zipf lookups, d = 256, Z = 8).  In the order by token, with two chains of additions
+// per run, it is at most 1.03 times the grouped deposit's, shape by shape, and 0.87
+// times in the mean (69 results of drawn and skewed shapes, three seeds each).
 #include <hip/hip_ext.h>
 
 #include "pss_keygen.hpp"
@@ -450,13 +450,18 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
       if (!SIGN || el.read) unsafeAtomicAdd(dst + el.m, SIGN ? apply_sign(x, el) : x);
     }
   };
-  float acc[EPL];
-#pragma unroll
-  for (int r = 0; r < EPL; ++r) acc[r] = 0.f;
+  // two chains of additions per run (a 32-bit sum of n terms in one chain rounds
+  // about as far off as sqrt(n / 2) last places)
+  float acc[2][EPL] = {};
   // the group's first run began in an earlier group's pairs
   bool head = q0 > 0 && nq > 0 && mk[q0] == mk[q0 - 1];
   bool tail = false;  // its last run goes on in the next group's pairs
   int start = q0;     // where its current run begins
+  float sum[EPL];
+  auto run_sum = [&] {
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) sum[r] = acc[0][r] + acc[1][r];
+  };
 #pragma unroll 1
   for (int u0 = 0; u0 < S; u0 += U) {
     if (u0 > 0) request(u0);
@@ -466,38 +471,46 @@ __global__ __launch_bounds__(4 * P) void deposit_pieces_kernel(
       if (u0 + u < nq) {
         const float f = __shfl(wf, base_lane + u0 + u);
 #pragma unroll
-        for (int r = 0; r < EPL; ++r) acc[r] += p.mean ? g[u][r] * f : g[u][r];
+        for (int r = 0; r < EPL; ++r) acc[u & 1][r] += p.mean ? g[u][r] * f : g[u][r];
         const bool ends = (ends_mask >> (u0 + u)) & 1u;
         tail = !ends;
         if (ends) {
+          run_sum();
           if (head) {
 #pragma unroll
-            for (int r = 0; r < EPL; ++r) headv[grp][LPB * r + gl] = acc[r];
+            for (int r = 0; r < EPL; ++r) headv[grp][LPB * r + gl] = sum[r];
             head = false;
           } else {
-            deposit(acc, start);
+            deposit(sum, start);
           }
           start = q + 1;
 #pragma unroll
-          for (int r = 0; r < EPL; ++r) acc[r] = 0.f;
+          for (int r = 0; r < EPL; ++r) acc[0][r] = acc[1][r] = 0.f;
         }
       }
     }
   }
+  run_sum();
   const bool thru = head && tail;  // all of its pairs lie inside one run
   if (thru) {
 #pragma unroll
-    for (int r = 0; r < EPL; ++r) headv[grp][LPB * r + gl] = acc[r];
+    for (int r = 0; r < EPL; ++r) headv[grp][LPB * r + gl] = sum[r];
   }
   if (gl == 0) through[grp] = thru ? 1u : 0u;
   __syncthreads();
   if (tail && !thru) {
-    for (int k = grp + 1; k < NG; ++k) {
+    float odd[EPL] = {};
+    for (int k = grp + 1; k < NG; k += 2) {
 #pragma unroll
-      for (int r = 0; r < EPL; ++r) acc[r] += headv[k][LPB * r + gl];
-      if (!through[k]) break;
+      for (int r = 0; r < EPL; ++r) odd[r] += headv[k][LPB * r + gl];
+      if (!through[k] || k + 1 >= NG) break;
+#pragma unroll
+      for (int r = 0; r < EPL; ++r) sum[r] += headv[k + 1][LPB * r + gl];
+      if (!through[k + 1]) break;
     }
-    deposit(acc, start);
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) sum[r] += odd[r];
+    deposit(sum, start);
   }
 }
 
@@ -546,8 +559,8 @@ static hipError_t launch_pieces_t(float* dst, float scale, const KParams& p, con
 // Pieces of 64 lookups for short regions, of 128 for longer ones, whose scan fewer
 // workgroups then repeat.  Backward, 64 / 128 (N lookups in regions of R): N = R = 1024 13.2 / 14.2 us,
 // 26 x 1024 18.3 / 21.5 us, 26 x 2048 28.7 / 28.3 us, N = R = 4096 20.4 / 17.4 us, 13 x 4096
-// 31.4 / 27.7 us.  256: N = R = 4096 21.0 us, 26 x 2048 35.7 us.
-constexpr uint32_t kSmallPieceRegion = 2048;
+// 31.4 / 27.7 us.  256: N = R = 8192 step 30.1 us against 27.2 by 128, 26 x 2048 backward 35.7 us.
+constexpr uint32_t kSmallPieceRegion = 1536;
 template <int EPL, int LPB, bool SIGN, bool REC, typename GT, typename... A>
 static hipError_t launch_pieces_p(float* dst, float scale, const KParams& p, A... a) {
   if (region_len(p) <= kSmallPieceRegion)
@@ -594,19 +607,24 @@ hipError_t launch_piece_records(float* sums, const KParams& p, const void* indic
 }
 
 // Where one kernel is the faster form of the deposit: one item per bag (the lookups of
-// a table are then T*B / T consecutive ones, and need no keygen), tables of
-// up to 4096 lookups (every workgroup scans its region) and up to 65536 lookups
-// in all.  Backward, pieces / grouped, uniform or Zipf(1.1) tokens of 10^7 rows, d = 128, Z = 32: 4 x 256 13.3 / 26 us,
-// 26 x 512 13.8 / 27.8 us, 1 x 4096 17.6 / 27.4 us, 26 x 2048 29 / 35.5 us, 13 x 4096
-// 27.9 / 34.2 us; 26 x 4096 52.1 / 52.1 us, of three tokens a table 34.2 / 26.1 us; 1 x 10240
-// 34 / 27.5 us; bags of 9 to 10 items 35 to 37 us (with its keygen) against 32 to 35 us.
+// a table are then T*B / T consecutive ones, and need no keygen), up to 65536
+// lookups, and regions for which the workgroups' scans (N / 112 of them, each of
+// a region) cost less than the sort's launches.  Backward, pieces / grouped, uniform or
+// Zipf(1.1) tokens of 10^7 rows, d = 128, Z = 32: 4 x 256 13.3 / 26 us, 26 x 512 13.8 / 27.8 us, 1 x
+// 4096 17.6 / 27.4 us, 26 x 2048 29 / 35.5 us, 13 x 4096 27.9 / 34.2 us; 26 x 4096 52.1 / 52.1 us, of three tokens a
+// table 34.2 / 26.1 us; bags of 9 to 10 items 35 to 37 us (with its keygen) against 32 to 35 us.
+// Training steps: 1 x 8192 27.2 / 31.7 us, 2 x 8192 28.1 / 32.9 us, 4 x 8192 36.1 / 35.6 us, 1 x 12288 32.5 / 32.8 us,
+// 1 x 16384 38.1 / 33.0 us, 6 x 10240 62.8 / 46.0 us.  Beyond 8192 lookups per table a token that
+// fills its table would also be rounded more often than by the grouped deposit.
 // A deposit costs a 64-byte line update at the memory side, about 20 G/s, for
 // every line of every chunk: the third bound keeps that below the chain's time.
 constexpr int64_t kPieceMaxItems = 1 << 16;
 constexpr int64_t kPieceMaxLines = 3 << 19;
-constexpr uint32_t kPieceRegion = 4096;
+constexpr uint32_t kPieceRegion = 8192;
+constexpr int64_t kPieceScans = 1 << 28;
 bool deposits_by_piece(const KParams& p) {
   return p.N <= kPieceMaxItems && keygen_counts(p) && region_len(p) <= kPieceRegion &&
+         p.N * region_len(p) <= kPieceScans &&
          p.N * static_cast<int64_t>(p.C) * (p.Z / 16 + 1) <= kPieceMaxLines;
 }
 

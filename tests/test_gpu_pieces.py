@@ -94,7 +94,8 @@ def test_piece_bags(case, kw):
 # and one more each (the last grouped); rows 1 and 2 divide every bin between
 # pieces, 40 some, 100000 none
 @pytest.mark.parametrize("T,B", [(1, 55), (1, 56), (1, 57), (5, 300), (7, 150), (2, 1024), (1, 2048),
-                                 (3, 2049), (2, 4096), (2, 4097), (16, 4096)])
+                                 (1, 1536),
+                                 (1, 1537), (3, 2049), (2, 4097), (16, 4096), (1, 8192), (1, 8193)])
 @pytest.mark.parametrize("kw", [{}, dict(sign="pm1", mean=True, idx32=True, flags=PREP)],
                          ids=["plain", "signed-prepared"])
 def test_piece_cuts(T, B, kw):
@@ -102,7 +103,7 @@ def test_piece_cuts(T, B, kw):
         wl = C2.scaled(T=T, B=B, d=16, Z=8, M=70_001, cardinality=f"fixed:{rows}")
         print(f"cuts T={T} B={B} rows={rows} {kw}", flush=True)
         L = Layer(wl, **kw)
-        assert L.route() == (pss.PSS_ROUTE_GROUPED if B > 4096 else pss.PSS_ROUTE_PIECES)
+        assert L.route() == (pss.PSS_ROUTE_GROUPED if B > 8192 else pss.PSS_ROUTE_PIECES)
         _step(L)
 
 
@@ -115,7 +116,7 @@ def _one_hot(T, B, tokens, **kw):
     return L
 
 
-@pytest.mark.parametrize("T,B", [(1, 1024), (4, 256), (1, 2048), (1, 4096), (13, 4096)])
+@pytest.mark.parametrize("T,B", [(1, 1024), (4, 256), (1, 2048), (1, 8192), (13, 4096)])
 def test_piece_rounding(T, B):
     """A token's lookups are summed before they are added to its weights, however they
     are spread over the batch: every token is read by 16 lookups, B / 16 apart, and each
@@ -147,7 +148,7 @@ def test_piece_rounding(T, B):
                                 dict(sign="sparse", rows_bf16=True, flags=PREP)],
                          ids=["pm1", "sparse-mean-i32", "bf16rows-mean", "i32-prep", "sparse-bf16rows-prep"])
 def test_grouped_options(d, Z, kw):
-    for B, card, bag in ((4500, "fixed:700", "one"), (1300, "fixed:40000", "poisson:4:0:30")):
+    for B, card, bag in ((8300, "fixed:700", "one"), (1300, "fixed:40000", "poisson:4:0:30")):
         wl = C2.scaled(T=1, B=B, d=d, Z=Z, M=50_000, cardinality=card, bag=bag, optimizer="adagrad")
         print(f"grouped d={d} Z={Z} B={B} {bag} {kw}", flush=True)
         L = Layer(wl, s0=0.1, **kw)
@@ -158,7 +159,7 @@ def test_grouped_options(d, Z, kw):
 @pytest.mark.parametrize("kw", [dict(mean=True), dict(mean=True, flags=PREP),
                                 dict(sign="pm1", mean=True, idx32=True, flags=PREP)],
                          ids=["plain", "prepared", "signed-i32-prepared"])
-@pytest.mark.parametrize("T,B", [(1, 4608), (2, 150_000)])
+@pytest.mark.parametrize("T,B", [(1, 8704), (2, 150_000)])
 def test_grouped_irregular_one_hot(T, B, kw):
     """As many items as bags, not one each: the keygen's bag search."""
     lengths = np.ones(T * B, dtype=np.int64)

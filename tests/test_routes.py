@@ -14,10 +14,12 @@ def _route(T, B, N, M, Z, d, flags=0, **kw):
 
 @pytest.mark.parametrize("T,B,N,Z,d,want", [
     (1, 1, 1, 4, 16, PIECES),
-    (1, 4096, 4096, 4, 16, PIECES),
-    (1, 4097, 4097, 4, 16, GROUPED),          # a table of more lookups than a region
-    (16, 4096, 65536, 16, 16, PIECES),
-    (17, 4096, 17 * 4096, 16, 16, GROUPED),   # more lookups
+    (1, 8192, 8192, 4, 16, PIECES),
+    (1, 8193, 8193, 4, 16, GROUPED),          # a table of more lookups than a region
+    (4, 8192, 32768, 16, 16, PIECES),
+    (5, 8192, 40960, 16, 16, GROUPED),        # more scanned
+    (64, 1024, 65536, 16, 16, PIECES),
+    (64, 1025, 65600, 16, 16, GROUPED),       # more lookups
     (26, 2048, 53248, 32, 128, PIECES),
     (1, 100, 101, 4, 16, GROUPED),            # several items per bag
     (4, 4096, 16384, 4, 384, PIECES),         # 1.5 M chunk lines
