@@ -455,7 +455,7 @@ hipError_t launch_update_tiles(const KParams& p, const void* indices, const void
 // costs a workgroup, and the list sums the counts of the tiles before) and
 // few enough records per tile (one workgroup adds them).  Kernel time of the call, general / by tile:
 // 8192 lookups, d = 64, Z = 16, 16 M elements 145 / 51 us; the list of 26 x 4096 Zipf lookups on 4 M
-// elements 141 / 83 us (79 us with records of the batch's own order, whose sums lie up to 1.23 times
+// elements 141 / 83 us (75 us with records of the batch's own order, whose sums lie up to 1.23 times
 // farther from 64-bit ones), 10240 uniform ones with d = 128, Z = 32 on 1.28 M elements 137 / 55 us.
 // The limits keep a margin to where the two meet (general / by tile, 8192 lookups, d = 64, Z = 16):
 // list of 4096 tiles 139 / 67 us, 8192 137 / 104 us, 16384 135 / 188 us; update of 16384

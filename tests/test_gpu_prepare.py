@@ -1,6 +1,6 @@
 """PSS_PREPARE_BACKWARD: the forward groups the batch for the next backward on
-the same stream, on a library stream, or (when it runs the streamed kernel)
-by writing the grouping's keygen stage itself.  Every result is checked
+the same stream, on a library stream, or (small batches, and those with as many
+items as bags) by making the grouping's keygen stage itself.  Every result is checked
 against the oracle, including the cases where the prepared grouping must not
 be used."""
 import numpy as np

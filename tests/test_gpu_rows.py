@@ -4,7 +4,8 @@ slabs (Sec. 2.4 forward, Sec. 2.5 mapping) against the oracle.
 A lane group of 4, 8, ... 64 lanes holds one row, 4 elements per lane when the
 chunk size is a multiple of 4 and one otherwise; wider rows are cut into
 slabs.  Batches with as many items as bags and other batches take different
-kernels, and one-hot batches of 2^20 bags on an array beyond 32 MiB a third.
+kernels, one-hot batches of 2^20 bags on an array beyond 32 MiB a third, and few
+long bags a fourth.
 """
 import numpy as np
 import pytest
